@@ -125,19 +125,6 @@ __device__ inline bool setup_work(const AttnArgs& a, Work& w, int D) {
   return true;
 }
 
-// Element offset of (token key, head kvh, element e) of the cached prefix.
-template <bool PAGED>
-__device__ inline int64_t cache_offset(const AttnArgs& a, int b, int kvh, int key, int e) {
-  int64_t off;
-  if (PAGED) {
-    const int64_t page = a.block_table[static_cast<int64_t>(b) * a.max_pages + key / a.page_size];
-    off = page * a.cs_seq + static_cast<int64_t>(key % a.page_size) * a.cs_tok;
-  } else {
-    off = static_cast<int64_t>(b) * a.cs_seq + static_cast<int64_t>(key) * a.cs_tok;
-  }
-  return off + static_cast<int64_t>(kvh) * a.cs_head + e;
-}
-
 // Partial layout per (pair, split): O[rows_pb][D] (unnormalised, fp32), then
 // m[rows_pb] (log2 units), then l[rows_pb].
 __device__ inline float* partial_base(const AttnArgs& a, const Work& w, int D) {
@@ -813,147 +800,332 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
 }
 
 // ----------------------------------------------------------------------------
-// float32 kernel (VALU).  A wave works on one row at a time (8 rows per wave,
-// 32 rows per work-group); the running output, max and sum of each row live
-// in LDS.  For a 16-key tile, lanes 16*q + j (q < 4) each take a quarter of
-// the dot product of key j; lanes own dims lane + 64*u of the output.
+// float32 kernel (fp32 matrix cores).  A work-group of four waves owns RB
+// 16-row blocks; each wave takes every fourth 16-key sub-tile of the range on
+// its own, with its own running output, max and sum, so the loop has no
+// barrier and stages nothing in LDS; the four states merge in LDS at the end.
+//
+// What bounds it: the fp32 products, 256 flop per cycle and CU (a 16-key
+// sub-tile is 2 * RB * D / 4 * 32 MFMA cycles per wave, 1.7 us at RB = 2 and
+// D = 128), while the next sub-tile's K and V load into a second register set.
+// Both products use v_mfma_f32_16x16x4_f32, whose operands are one float per
+// lane, so a lane's 16-byte loads become operands as they are:
+//   S^T = K Q^T: lane (n = lane % 16, q = lane / 16) holds dims 16 i + 4 q + e
+//     of key n (register e of load i), and of query row n: MFMA (i, e)
+//     contracts dims 16 i + 4 {0..3} + e.
+//   O^T += V^T P^T: MFMA j contracts keys 4 {0..3} + j.  Register j of the
+//     scores is key 4 q + j of row n already, the B operand without a shuffle;
+//     the V^T operand is key 4 q + j, dim 64 u + 4 n + e, register e of the
+//     16-byte load (j, u).
+// Measured, kernel time at batch 1, 32/8 heads, D 128, 16 new slots: prefix 1024
+// 11.8 us (54.9 us with fp32 vector FMAs and per-row state in LDS, the kernel
+// this one replaced); prefix 8192 with 64 new slots 105 us, 83 TFLOP/s of the
+// 153 a large fp32 matrix product reaches.
 // ----------------------------------------------------------------------------
-template <int D, bool PAGED>
-__global__ void __launch_bounds__(256) attn_f32_kernel(AttnArgs a) {
-  constexpr int NT = 256, TK = 16, RPW = 8, KROW = D + 1, DU = D / 64, QD = D / 4;
-  __shared__ float sk[TK * KROW];
-  __shared__ float sv[TK * D];
-  __shared__ float sq[32 * D];
-  __shared__ float so[32 * D];
-  __shared__ float sm[32], sl[32];
+__device__ inline float quad_max(float x) {      // over lanes l, l ^ 16, l ^ 32, l ^ 48
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return xhalf_max(fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1])));
+}
+__device__ inline float quad_sum(float x) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return xhalf_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+template <int D, int RB, bool PAGED, bool ROPE>
+__global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
+  constexpr int NW = 4, SUB = 16;              // waves; keys per sub-tile
+  constexpr int KI = D / 16;                   // 16-byte loads per lane of a K (or Q) row
+  constexpr int VU = D / 64;                   // 16-byte loads per lane of a V key
+  constexpr int ROWS = 16 * RB;
+  constexpr int XROW = D + 4;                  // LDS row stride of the merge (floats)
+  // The waves' outputs at the end; before the loop (ROPE), the rotated queries,
+  // then the rotated new keys.
+  constexpr int XROWS = NW * ROWS > kMaxNew ? NW * ROWS : kMaxNew;
+  __shared__ __attribute__((aligned(16))) float xs[XROWS * XROW];
+  __shared__ float s_m[NW][ROWS], s_l[NW][ROWS];
   __shared__ uint64_t vis[kMaxNew];
   __shared__ int s_pos[kMaxNew];
 
   Work w;
   if (!setup_work(a, w, D)) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n = lane & 15, q = lane >> 4;
+  const int m0 = w.rb * ROWS;
   const int32_t* step_row = a.step_map + static_cast<int64_t>(w.b) * a.B;
   const int lane_step = step_row[min(lane, a.B - 1)];
-  build_visibility<NT / 64>(vis, lane_step, w.gamma, a.B, a.n_new, wave, lane);
-  if (a.rope) {
-    if (wave == 0) build_positions(s_pos, lane_step, w.gamma, a.B, a.L, w.plen, lane);
-    __syncthreads();
-  }
-  // Rotary embedding of element e of a new slot's row x (fp64 angles: this is
-  // the exact path): dims e and e +- D/2 form the pair.
-  auto rotated = [&](const float* x, int e, int slot) -> float {
-    const float v = x[e];
-    if (!a.rope) return v;
-    const int i = e % (D / 2);
-    const float partner = x[e < D / 2 ? e + D / 2 : e - D / 2];
-    const double ang = static_cast<double>(s_pos[slot]) * pow(static_cast<double>(a.rope_theta), -2.0 * i / D);
-    const double c = cos(ang), sn = sin(ang);
-    return static_cast<float>(e < D / 2 ? v * c - partner * sn : v * c + partner * sn);
+  const float* qb = static_cast<const float*>(a.q);
+  auto q_row = [&](int m) -> const float* {
+    const int t = m / a.group, hq = w.kvh * a.group + m % a.group;
+    return qb + ((static_cast<int64_t>(w.b) * a.n_new + t) * a.hq + hq) * D;
   };
-  if (tid < 32) {
-    sm[tid] = kNegInf;
-    sl[tid] = 0.f;
-  }
-  for (int idx = tid; idx < 32 * D; idx += NT) {
-    const int rowl = idx / D, d = idx % D;
-    const int m = w.rb * a.rows_pb + rowl;
-    float v = 0.f;
-    if (m < a.rows) {
-      const int t = m / a.group, hq = w.kvh * a.group + m % a.group;
-      v = rotated(static_cast<const float*>(a.q) + ((static_cast<int64_t>(w.b) * a.n_new + t) * a.hq + hq) * D, d, t);
+
+  // Sub-tiles of this wave: prefix sub-tiles wave, wave + 4, ..., then (when
+  // has_new) new slots 16 * wave .. 16 * wave + 15.
+  const int nsub = w.kend > w.kbeg ? (w.kend - w.kbeg + SUB - 1) / SUB : 0;
+  const bool my_new = w.has_new && SUB * wave < a.n_new;
+  const int64_t new0 = (static_cast<int64_t>(w.b) * a.n_new * a.hkv + w.kvh) * D;
+  const int64_t newrow = static_cast<int64_t>(a.hkv) * D;
+  const float* kn = static_cast<const float*>(a.k_new) + new0;
+  const int64_t seq0 = (PAGED ? 0 : w.b * a.cs_seq) + w.kvh * a.cs_head;
+  const float* kc = static_cast<const float*>(a.k_cache) + seq0;
+  const int32_t* pages = a.block_table + static_cast<int64_t>(w.b) * a.max_pages;
+  // Item i of this wave: prefix sub-tile wave + 4 i, or (the last, when
+  // my_new) its new slots.
+  const int np = nsub > wave ? (nsub - wave + NW - 1) / NW : 0;
+  const int items = np + (my_new ? 1 : 0);
+  // Address of key `key` of an item, `base` and the rest uniform: keys past the
+  // item's last one read that one (their scores are masked and their values
+  // finite).  Prefix and new slots differ in the uniform values only.
+  auto key_at = [&](const float* base, bool is_new, int key, int page) __attribute__((always_inline)) {
+    const int64_t st = is_new ? newrow : a.cs_tok;
+    key = min(key, is_new ? a.n_new - 1 : w.kend - 1);
+    if (!PAGED) return base + key * st;
+    const int64_t pst = is_new ? 0 : a.cs_seq;
+    return base + (page * pst + (key % (is_new ? kMaxNew : a.page_size)) * st);
+  };
+  auto key0 = [&](int i) { return i < np ? w.kbeg + SUB * (wave + NW * i) : SUB * wave; };
+  f32x4 kx[KI], vx[SUB / 4][VU];
+  int page = 0, page_v = 0;                    // of key n: of the K loads ahead, of the V loads ahead
+  auto next_page = [&](int i) __attribute__((always_inline)) {
+    if (PAGED && i < np) page = pages[min(key0(i) + n, w.kend - 1) / a.page_size];
+  };
+  auto load_k = [&](int i) __attribute__((always_inline)) {
+    const bool is_new = i >= np;
+    if (ROPE && is_new) {                      // rotated in LDS
+      const float* kr = &xs[min(SUB * wave + n, a.n_new - 1) * XROW + 4 * q];
+#pragma unroll
+      for (int c = 0; c < KI; ++c) kx[c] = *reinterpret_cast<const f32x4*>(kr + 16 * c);
+      return;
     }
-    sq[idx] = v;
-    so[idx] = 0.f;
+    const f32x4* kr = reinterpret_cast<const f32x4*>(key_at(is_new ? kn : kc, is_new, key0(i) + n, page));
+#pragma unroll
+    for (int c = 0; c < KI; ++c) kx[c] = kr[4 * c + q];
+    page_v = page;
+    next_page(i + 1);
+  };
+  auto load_v = [&](int i) __attribute__((always_inline)) {
+    const bool is_new = i >= np;
+    const float* base = is_new ? static_cast<const float*>(a.v_new) + new0
+                               : static_cast<const float*>(a.v_cache) + seq0;
+#pragma unroll
+    for (int j = 0; j < SUB / 4; ++j) {
+      const int pj = PAGED ? __shfl(page_v, 4 * q + j) : 0;
+      const f32x4* vr = reinterpret_cast<const f32x4*>(key_at(base, is_new, key0(i) + 4 * q + j, pj));
+#pragma unroll
+      for (int u = 0; u < VU; ++u) vx[j][u] = vr[16 * u + n];
+    }
+  };
+
+  // The first item's loads go out before anything else is waited for (rotated
+  // new keys are not in LDS yet: they are read below).
+  if (items > 0 && (!ROPE || np > 0)) {
+    next_page(0);
+    load_k(0);
+    load_v(0);
   }
 
-  const float sl2 = a.scale_log2;
-  const int ntp = w.kend > w.kbeg ? (w.kend - w.kbeg + TK - 1) / TK : 0;
-  const int ntn = w.has_new ? (a.n_new + TK - 1) / TK : 0;
-  const int j = lane & 15, qtr = lane >> 4;
-  for (int it = 0; it < ntp + ntn; ++it) {
-    const bool is_new = it >= ntp;
-    const int k0 = is_new ? (it - ntp) * TK : w.kbeg + it * TK;
+  // Query operands: row m0 + 16 r + n, dims 16 i + 4 q + e.
+  f32x4 qop[RB][KI];
+  if constexpr (!ROPE) {
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const int m = m0 + 16 * r + n;
+      const f32x4* qr = reinterpret_cast<const f32x4*>(q_row(min(m, a.rows - 1)));
+#pragma unroll
+      for (int i = 0; i < KI; ++i) qop[r][i] = qr[4 * i + q];
+    }
+  }
+  build_visibility<NW>(vis, lane_step, w.gamma, a.B, a.n_new, wave, lane);
+  if constexpr (ROPE) {
+    if (wave == 0) build_positions(s_pos, lane_step, w.gamma, a.B, a.L, w.plen, lane);
     __syncthreads();
-    for (int idx = tid; idx < TK * D; idx += NT) {
-      const int row = idx / D, e = idx % D;
-      float kv = 0.f, vv = 0.f;
-      if (is_new) {
-        const int slot = k0 + row;
-        if (slot < a.n_new) {
-          const int64_t off = ((static_cast<int64_t>(w.b) * a.n_new + slot) * a.hkv + w.kvh) * D;
-          kv = rotated(static_cast<const float*>(a.k_new) + off, e, slot);
-          vv = static_cast<const float*>(a.v_new)[off + e];
-        }
-      } else if (k0 + row < w.kend) {
-        const int64_t off = cache_offset<PAGED>(a, w.b, w.kvh, k0 + row, e);
-        kv = static_cast<const float*>(a.k_cache)[off];
-        vv = static_cast<const float*>(a.v_cache)[off];
-      }
-      sk[row * KROW + e] = kv;
-      sv[row * D + e] = vv;
+    // Rotary embedding with fp64 angles (this is the exact path): dims i and
+    // i + D/2 of a slot turn by the same angle, formed once for the query heads
+    // of the slot.
+    auto turn = [&](int slot, int i, double& c, double& sn) {
+      const double ang = static_cast<double>(s_pos[slot]) * pow(static_cast<double>(a.rope_theta), -2.0 * i / D);
+      c = cos(ang);
+      sn = sin(ang);
+    };
+    auto rotate = [&](const float* x, float* y, int i, double c, double sn) {
+      const float lo = x[i], hi = x[i + D / 2];
+      y[i] = static_cast<float>(lo * c - hi * sn);
+      y[i + D / 2] = static_cast<float>(hi * c + lo * sn);
+    };
+    const int m1 = min(m0 + ROWS, a.rows);
+    const int t0 = m0 / a.group, nt = (m1 - 1) / a.group - t0 + 1;
+    for (int idx = tid; idx < nt * (D / 2); idx += NW * 64) {
+      const int t = t0 + idx / (D / 2), i = idx % (D / 2);
+      double c, sn;
+      turn(t, i, c, sn);
+      for (int m = max(t * a.group, m0); m < min((t + 1) * a.group, m1); ++m)
+        rotate(q_row(m), &xs[(m - m0) * XROW], i, c, sn);
     }
     __syncthreads();
-    for (int r = 0; r < RPW; ++r) {
-      const int rowl = wave * RPW + r;
-      const int m = w.rb * a.rows_pb + rowl;
-      const uint64_t rv = m < a.rows ? vis[m / a.group] : 0ull;
-      float s = 0.f;
-      for (int d = 0; d < QD; ++d) s = fmaf(sq[rowl * D + qtr * QD + d], sk[j * KROW + qtr * QD + d], s);
-      s += __shfl_xor(s, 16);
-      s += __shfl_xor(s, 32);
-      const bool ok = is_new ? ((rv >> (k0 + j)) & 1ull) != 0ull : (k0 + j < w.kend);
-      s = ok ? s * sl2 : kNegInf;
-      float mx = s;
 #pragma unroll
-      for (int sh = 8; sh >= 1; sh >>= 1) mx = fmaxf(mx, __shfl_xor(mx, sh));
-      const float m_old = sm[rowl];
-      const float m_new = fmaxf(m_old, mx);
-      const float moff = m_new == kNegInf ? 0.f : m_new;
-      const float alpha = __builtin_amdgcn_exp2f(m_old - moff);
-      const float p = __builtin_amdgcn_exp2f(s - moff);
-      float ps = p;
+    for (int r = 0; r < RB; ++r) {
+      const int row = min(16 * r + n, m1 - 1 - m0);
 #pragma unroll
-      for (int sh = 8; sh >= 1; sh >>= 1) ps += __shfl_xor(ps, sh);
-      float acc[DU];
-#pragma unroll
-      for (int u = 0; u < DU; ++u) acc[u] = so[rowl * D + lane + 64 * u] * alpha;
-      for (int jj = 0; jj < TK; ++jj) {
-        const float pj = __shfl(p, jj);
-#pragma unroll
-        for (int u = 0; u < DU; ++u) acc[u] = fmaf(pj, sv[jj * D + lane + 64 * u], acc[u]);
+      for (int i = 0; i < KI; ++i) qop[r][i] = *reinterpret_cast<const f32x4*>(&xs[row * XROW + 16 * i + 4 * q]);
+    }
+    if (w.has_new) {
+      __syncthreads();                         // the query reads are done
+      for (int idx = tid; idx < a.n_new * (D / 2); idx += NW * 64) {
+        const int t = idx / (D / 2), i = idx % (D / 2);
+        double c, sn;
+        turn(t, i, c, sn);
+        rotate(kn + t * newrow, &xs[t * XROW], i, c, sn);
       }
+    }
+  }
+  __syncthreads();                             // visibility words, rotated keys
+  if (ROPE && np == 0 && items > 0) {
+    load_k(0);
+    load_v(0);
+  }
+
+  f32x4 o[RB][D / 16];
+  float m_run[RB], l_run[RB];
 #pragma unroll
-      for (int u = 0; u < DU; ++u) so[rowl * D + lane + 64 * u] = acc[u];
-      if (lane == 0) {
-        sl[rowl] = sl[rowl] * alpha + ps;
-        sm[rowl] = m_new;
+  for (int r = 0; r < RB; ++r) {
+#pragma unroll
+    for (int c = 0; c < D / 16; ++c) o[r][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[r] = kNegInf;
+    l_run[r] = 0.f;
+  }
+  const float sl2 = a.scale_log2;
+
+  // One item per round: scores of its 16 keys, the rows' running state, the
+  // output.  Its K registers are free after the scores and its V registers
+  // after the output, so the next item's K loads run under this one's V
+  // product and its V loads under the next scores (the scheduling barriers
+  // keep the loads from moving up, which would take a second register set).
+  for (int it = 0; it < items; ++it) {
+    const bool is_new = it >= np;
+    const int k0 = is_new ? SUB * wave : w.kbeg + SUB * (wave + NW * it);
+    // Four partial sums of D / 4 dims each, added up as they end: shorter
+    // rounding chains than one sum over all D.
+    f32x4 s[RB];
+#pragma unroll
+    for (int r = 0; r < RB; ++r) s[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      f32x4 sp[RB];
+#pragma unroll
+      for (int r = 0; r < RB; ++r) sp[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int i = c * KI / 4; i < (c + 1) * KI / 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int r = 0; r < RB; ++r)
+            sp[r] = __builtin_amdgcn_mfma_f32_16x16x4f32(kx[i][e], qop[r][i][e], sp[r], 0, 0, 0);
+#pragma unroll
+      for (int r = 0; r < RB; ++r) s[r] += sp[r];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    if (it + 1 < items) load_k(it + 1);
+    if (is_new) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r) {
+        const int m = m0 + 16 * r + n;
+        const uint64_t see = m < a.rows ? vis[m / a.group] : 0ull;
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (!((see >> (k0 + 4 * q + j)) & 1ull)) s[r][j] = kNegInf;
       }
+    } else if (k0 + SUB > w.kend) {
+#pragma unroll
+      for (int r = 0; r < RB; ++r)
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+          if (k0 + 4 * q + j >= w.kend) s[r][j] = kNegInf;
+    }
+#pragma unroll
+    for (int r = 0; r < RB; ++r) {
+      const float mx = quad_max(fmaxf(fmaxf(s[r][0], s[r][1]), fmaxf(s[r][2], s[r][3])));
+      const float m_new = fmaxf(m_run[r], mx * sl2);
+      if (m_new > m_run[r] + kLazy) {
+        const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
+        l_run[r] *= alpha;
+#pragma unroll
+        for (int c = 0; c < D / 16; ++c) o[r][c] *= alpha;
+        m_run[r] = m_new;
+      }
+      const float moff = m_run[r] == kNegInf ? 0.f : m_run[r];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        s[r][j] = __builtin_amdgcn_exp2f(fmaf(s[r][j], sl2, -moff));
+        l_run[r] += s[r][j];
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int u = 0; u < VU; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int r = 0; r < RB; ++r)
+            o[r][4 * u + e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vx[j][u][e], s[r][j], o[r][4 * u + e], 0, 0, 0);
+    __builtin_amdgcn_sched_barrier(0);
+    if (it + 1 < items) load_v(it + 1);
+  }
+
+  // Merge of the four waves' states.
+#pragma unroll
+  for (int r = 0; r < RB; ++r) l_run[r] = quad_sum(l_run[r]);
+  if (ROPE) __syncthreads();                   // the rotated keys are no longer read
+#pragma unroll
+  for (int r = 0; r < RB; ++r) {
+    const int row = 16 * r + n;
+    // Register t of o[r][4 u + e] holds dim 64 u + 16 q + 4 t + e of this row.
+    float* x = &xs[(wave * ROWS + row) * XROW + 16 * q];
+#pragma unroll
+    for (int u = 0; u < VU; ++u)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        *reinterpret_cast<f32x4*>(x + 64 * u + 4 * t) =
+            f32x4{o[r][4 * u][t], o[r][4 * u + 1][t], o[r][4 * u + 2][t], o[r][4 * u + 3][t]};
+    if (q == 0) {
+      s_m[wave][row] = m_run[r];
+      s_l[wave][row] = l_run[r];
     }
   }
   __syncthreads();
-
-  if (w.final) {
-    for (int r = 0; r < RPW; ++r) {
-      const int rowl = wave * RPW + r;
-      const int m = w.rb * a.rows_pb + rowl;
-      if (m >= a.rows) continue;
+  for (int idx = tid; idx < ROWS * (D / 4); idx += NW * 64) {
+    const int row = idx / (D / 4), d0 = 4 * (idx % (D / 4));
+    const int m = m0 + row;
+    if (m >= a.rows) continue;
+    float mt = kNegInf;
+#pragma unroll
+    for (int g = 0; g < NW; ++g) mt = fmaxf(mt, s_m[g][row]);
+    const float mref = mt == kNegInf ? 0.f : mt;
+    f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    float l = 0.f;
+#pragma unroll
+    for (int g = 0; g < NW; ++g) {
+      const float wt = __builtin_amdgcn_exp2f(s_m[g][row] - mref);
+      acc += wt * *reinterpret_cast<const f32x4*>(&xs[(g * ROWS + row) * XROW + d0]);
+      l += wt * s_l[g][row];
+    }
+    if (w.final) {
       const int t = m / a.group, hq = w.kvh * a.group + m % a.group;
       const bool valid = vis[t] != 0ull;
-      const float inv = valid ? 1.f / sl[rowl] : 0.f;
-      float* orow = static_cast<float*>(a.out) + ((static_cast<int64_t>(w.b) * a.n_new + t) * a.hq + hq) * D;
-#pragma unroll
-      for (int u = 0; u < DU; ++u) orow[lane + 64 * u] = so[rowl * D + lane + 64 * u] * inv;
-      if (a.lse && lane == 0)
+      const float inv = valid ? 1.f / l : 0.f;
+      *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) +
+                                ((static_cast<int64_t>(w.b) * a.n_new + t) * a.hq + hq) * D + d0) = acc * inv;
+      if (a.lse && d0 == 0)
         a.lse[(static_cast<int64_t>(w.b) * a.hq + hq) * a.n_new + t] =
-            valid ? (sm[rowl] + __log2f(sl[rowl])) * kLn2 : kNegInf;
+            valid ? (mt + __log2f(l)) * kLn2 : kNegInf;
+    } else {
+      *reinterpret_cast<f32x4*>(w.part + row * D + d0) = acc;
+      if (d0 == 0) {
+        w.part[ROWS * D + row] = mt;
+        w.part[ROWS * D + ROWS + row] = l;
+      }
     }
-    return;
-  }
-  float* part = w.part;
-  for (int idx = tid; idx < 32 * D; idx += NT) part[idx] = so[idx];
-  if (tid < 32) {
-    part[a.rows_pb * D + tid] = sm[tid];
-    part[a.rows_pb * D + a.rows_pb + tid] = sl[tid];
   }
 }
 
@@ -1157,10 +1329,23 @@ inline int merge_dims(const AttnPlan& p, bool bf16) {
   return bf16 && (p.stream || p.splits <= 8) ? 8 : 4;
 }
 
+template <int D, bool PAGED, bool ROPE>
+void launch_f32_rows(const AttnPlan& p, dim3 grid, const AttnArgs& a, hipStream_t st) {
+  switch (p.rows_pb) {
+    case 16: hipLaunchKernelGGL((attn_f32_kernel<D, 1, PAGED, ROPE>), grid, dim3(256), 0, st, a); break;
+    default: hipLaunchKernelGGL((attn_f32_kernel<D, 2, PAGED, ROPE>), grid, dim3(256), 0, st, a); break;
+  }
+}
+
 template <int D>
-void launch_f32(bool paged, dim3 grid, const AttnArgs& a, hipStream_t st) {
-  if (paged) hipLaunchKernelGGL((attn_f32_kernel<D, true>), grid, dim3(256), 0, st, a);
-  else hipLaunchKernelGGL((attn_f32_kernel<D, false>), grid, dim3(256), 0, st, a);
+void launch_f32(bool paged, const AttnPlan& p, dim3 grid, const AttnArgs& a, hipStream_t st) {
+  if (paged) {
+    if (a.rope) launch_f32_rows<D, true, true>(p, grid, a, st);
+    else launch_f32_rows<D, true, false>(p, grid, a, st);
+  } else {
+    if (a.rope) launch_f32_rows<D, false, true>(p, grid, a, st);
+    else launch_f32_rows<D, false, false>(p, grid, a, st);
+  }
 }
 
 }  // namespace
@@ -1178,8 +1363,8 @@ hipError_t launch_attention(const simsd_attn_desc& d, const AttnPlan& p, const A
       else launch_bf16<64, false>(p, grid, a, st);
     }
   } else {
-    if (d.head_dim == 128) launch_f32<128>(paged, grid, a, st);
-    else launch_f32<64>(paged, grid, a, st);
+    if (d.head_dim == 128) launch_f32<128>(paged, p, grid, a, st);
+    else launch_f32<64>(paged, p, grid, a, st);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || (p.splits <= 1 && !p.stream)) return e;

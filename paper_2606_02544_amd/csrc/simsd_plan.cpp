@@ -99,9 +99,11 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     r.waves = r.row_waves <= 2 ? 2 * r.row_waves : r.row_waves;
     r.rows_pb = r.row_waves * 32;
   } else {
-    r.waves = 4;          // 8 rows per wave, one wave per row at a time
+    // One or two 16-row blocks per work-group, whose four waves split the
+    // keys; two groups per CU.
+    r.waves = 4;
     r.row_waves = 4;
-    r.rows_pb = 32;
+    r.rows_pb = r.rows <= 16 ? 16 : 32;
   }
   r.row_blocks = static_cast<int>(ceil_div(r.rows, r.rows_pb));
   if (static_cast<int64_t>(d->num_kv_heads) * r.row_blocks > 65535)
@@ -111,8 +113,9 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     r.chunk = d->kv_chunk;
   } else {
     // Split the longest prefix so that about as many work-groups exist as the
-    // chip holds at once: one group per CU, two for the two-row-wave groups.
-    const int64_t target = r.row_waves >= 4 ? cus : 2 * int64_t{cus};
+    // chip holds at once: one group per CU, two for the two-row-wave groups
+    // and the fp32 ones.
+    const int64_t target = d->dtype == SIMSD_BF16 && r.row_waves >= 4 ? cus : 2 * int64_t{cus};
     int64_t c = ceil_div(static_cast<int64_t>(d->max_prefix_len) * r.pairs, target);
     c = ceil_div(c, kTile) * kTile;
     if (c < kMinAutoChunk) c = kMinAutoChunk;

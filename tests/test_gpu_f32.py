@@ -1,0 +1,39 @@
+"""GPU parity of the fp32 attention kernel at the edges of its tiling: 16-key
+sub-tiles dealt to four waves, work-groups of one or two 16-row blocks, the new
+slots as one more sub-tile per wave.  Same tolerance as the other fp32 tests
+(1e-5 absolute: outputs are averages of N(0, 1) values, so a sum over n keys is
+off by a few ulps of 1, about sqrt(n) * 6e-8 < 2e-6 at n = 1100)."""
+
+import pytest
+
+import oracle
+from gpu_util import DeviceInputs, run_attention, check_attention
+from synth import VerifyConfig, generate
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # head_dim, Hq, Hkv, B, L, prefix, page, kv_chunk, theta
+    (128, 1, 1, 1, 0, (1, 1), 0, 0, 0.0),          # one row, one key: three waves idle
+    (128, 2, 1, 4, 4, (15, 17), 0, 0, 0.0),        # 16 rows; around one sub-tile
+    (128, 4, 2, 8, 1, (63, 65), 16, 0, 0.0),       # 18 rows: two blocks, around a chunk
+    (128, 4, 1, 8, 1, (0, 40), 3, 0, 0.0),         # 36 rows: a second, partial row block
+    (64, 16, 1, 1, 1, (47, 130), 0, 64, 0.0),      # 32 rows exactly, several splits
+    (64, 8, 8, 32, 32, (0, 200), 64, 128, 0.0),    # 64 new slots: a sub-tile on every wave
+    (128, 16, 2, 24, 24, (300, 1100), 16, 0, 0.0),  # 384 rows, long ranges per wave
+    (128, 2, 2, 8, 8, (0, 100), 0, 64, 1e6),       # rotary: 16 rows, has_new with no prefix items
+    (64, 12, 2, 17, 16, (5, 333), 8, 64, 1e4),     # rotary: slots shared by two row blocks
+    (128, 3, 1, 32, 32, (0, 90), 0, 0, 1e6),       # rotary: 64 rotated keys, 192 rows
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+def test_f32_tiles(case):
+    d, hq, hkv, B, L, prefix, page, kv_chunk, theta = case
+    cfg = VerifyConfig(0, "f32", "f32", batch=4, num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
+                       prefix=prefix, block_size=B, max_ref=L, vocab=100, page_size=page,
+                       qkv_std=1.0, step_mode="mixed" if L else "full")
+    inp = generate(cfg, seed=500 + d + B, poison=True)
+    out, lse = run_attention(DeviceInputs(inp), kv_chunk, rope_theta=theta)
+    ref_out, ref_lse = oracle.verify_attention(inp, rope_theta=theta)
+    check_attention(out, lse, ref_out, ref_lse, "f32")
