@@ -120,6 +120,7 @@ extern "C" simsd_status simsd_verify_attention(
                                                           static_cast<size_t>(p.stream_groups) * 2 *
                                                               p.part_floats * 4)
                              : nullptr;
+    a.seg_tiles = p.seg_tiles;
     a.batch = desc->batch;
     a.cs_seq = desc->cache_stride_seq;
     a.cs_tok = desc->cache_stride_token;

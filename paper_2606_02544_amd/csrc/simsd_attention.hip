@@ -719,13 +719,15 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_kernel(AttnArgs a) 
 
 // Stream decomposition, for large and ragged batches.  The tiles of all
 // pairs form one sequence: pair q = kvh * row_blocks + rb of sequence b owns
-// tp_b consecutive tiles (its prefix tiles, then the new-slot tile) starting
-// at seq0[b] + q * tp_b.  Work-group g of G takes tiles [g*T/G, (g+1)*T/G),
-// so every group gets the same number of tiles however ragged the prefixes
-// are (G = min(grid, T), so no range is empty); it attends over each pair's part of its range in turn.  A part that
-// covers a whole pair writes the output; the others write partials to the
-// group's two slots (0: the part at the start of its range, 1: the part at
-// its end), which the merge kernel locates from the same arithmetic.
+// tp_b consecutive entries (its prefix tiles, the new-slot tile, then
+// seg_tiles entries that stand for its set-up and hold no work) starting at
+// seq0[b] + q * tp_b.  Work-group g of G takes entries [g*T/G, (g+1)*T/G), so
+// every group gets about the same time however ragged the prefixes are
+// (G = min(grid, T), so no range is empty); it attends over each pair's part
+// of its range in turn.  A part that covers a whole pair writes the output;
+// the others write partials to the group's two slots (0: the part at the
+// start of its range, 1: the part at its end), which the merge kernel locates
+// from the same arithmetic.
 // seq0[0..batch] (int64) in LDS, and (group 0) in the workspace for the merge.
 __device__ inline void stream_offsets(const AttnArgs& a, int64_t* seq0) {
   const int tid = threadIdx.x;
@@ -734,7 +736,7 @@ __device__ inline void stream_offsets(const AttnArgs& a, int64_t* seq0) {
     int64_t v = 0;
     if (tid < a.batch) {
       const int plen = min(max(a.prefix_lens[tid], 0), a.max_prefix);
-      v = static_cast<int64_t>(pps) * ((plen + kTile - 1) / kTile + 1);
+      v = static_cast<int64_t>(pps) * ((plen + kTile - 1) / kTile + 1 + a.seg_tiles);
     }
     seq0[tid + 1] = v;
   }
@@ -779,7 +781,11 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
     const int q = static_cast<int>(local / tp);
     const int t0 = static_cast<int>(local % tp);
     const int t1 = static_cast<int>(min(tp, t0 + (hi - x)));
-    const int ntp = static_cast<int>(tp) - 1;
+    const int ntp = static_cast<int>(tp) - 1 - a.seg_tiles;
+    if (t0 > ntp) {                            // only the pair's set-up weight is left
+      x += t1 - t0;
+      continue;
+    }
     Work w;
     w.b = b;
     w.kvh = q / a.row_blocks;
@@ -790,8 +796,8 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
     w.gamma = min(max(a.num_ref[b], 0), a.L);
     w.kbeg = min(t0, ntp) * kTile;
     w.kend = min(min(t1, ntp) * kTile, w.plen);
-    w.has_new = t1 == tp;
-    w.final = t0 == 0 && t1 == tp;
+    w.has_new = t1 > ntp;
+    w.final = t0 == 0 && w.has_new;
     w.part = a.part + (static_cast<int64_t>(g) * 2 + (x == lo ? 0 : 1)) *
                           static_cast<int64_t>(a.rows_pb) * (D + 2);
     attend_segment<D, RW, KW, PAGED, ROPE>(a, w);
@@ -1177,11 +1183,11 @@ __global__ void __launch_bounds__(256) merge_kernel(AttnArgs a) {
     const int64_t sb = a.stream_seq0[b + lane_zero], se = a.stream_seq0[b + 1 + lane_zero];
     T = a.stream_seq0[a.batch + lane_zero];
     G = static_cast<int>(min<int64_t>(a.stream_groups, T));   // the working groups
-    const int64_t tp = (se - sb) / (a.hkv * a.row_blocks);
+    const int64_t tp = (se - sb) / (a.hkv * a.row_blocks);   // its last seg_tiles entries hold no work
     start = sb + static_cast<int64_t>(kvh * a.row_blocks + rb) * tp;
     // owner(x) = the group g with g*T/G <= x < (g+1)*T/G
     g_first = static_cast<int>(((start + 1) * G - 1) / T);
-    const int g_last = static_cast<int>(((start + tp) * G - 1) / T);
+    const int g_last = static_cast<int>(((start + tp - a.seg_tiles) * G - 1) / T);
     nsplit = g_last - g_first + 1;
   } else {
     const int plen = min(max(a.prefix_lens[b + lane_zero], 0), a.max_prefix);

@@ -27,6 +27,7 @@ struct AttnArgs {
   int batch, hq, hkv, group, B, L, n_new, rows, rows_pb, row_blocks;
   int page_size, max_pages, chunk, splits, max_prefix;
   int stream_groups;  // stream decomposition: work-groups (0 = chunked decomposition)
+  int seg_tiles;      // stream decomposition: tiles a pair's set-up counts for
   float scale_log2;
   int rope;           // rotary embedding of the new slots' q and k at the RoPE-copy positions
   float rope_step;    // pair i turns by pos * exp2(i * rope_step)

@@ -146,6 +146,15 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     if (d->kv_chunk == kStreamChunk || (tiles >= 8 * groups && r.pairs * r.splits > groups)) {
       r.stream = true;
       r.stream_groups = static_cast<int>(groups);
+      // A pair costs its group a set-up besides its tiles (its loads in turn,
+      // the ring filled and drained, the output written), which short
+      // prefixes repeat most.  The ranges count it as this many tiles.
+      // Attention kernel, 24 sequences with prefixes 101..6007: 108 packed
+      // rows, paged, rotary, 134 us at 0, 122 at 2, 108 at 4, 98 at 8, 98 at
+      // 12, 104 at 16; 64 rows, 81 us at 0, 72 at 2, 71 at 4, 72 at 8, 75 at
+      // 16 (two groups per CU: one's set-up runs beside the other's tiles).
+      // 64 sequences with prefixes 512..32768: 820 us at 0, 812 at 4.
+      r.seg_tiles = r.row_waves >= 4 ? 8 : 4;
       r.workspace = static_cast<size_t>(groups) * 2 * r.part_floats * 4 +
                     static_cast<size_t>(kMaxStreamBatch + 1) * 8;
     }

@@ -32,6 +32,7 @@ struct AttnPlan {
   int splits = 0;       // grid.x: ceil(max_prefix_len / chunk), >= 1
   bool stream = false;  // bf16: stream decomposition (equal tile ranges per work-group)
   int stream_groups = 0;
+  int seg_tiles = 0;    // stream: tiles that one pair's set-up counts for in the ranges
   int64_t pairs = 0;    // batch * Hkv * row_blocks
   size_t part_floats = 0;   // floats per split partial: rows_pb * (head_dim + 2)
   size_t workspace = 0;     // total bytes

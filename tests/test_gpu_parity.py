@@ -175,6 +175,21 @@ def test_max_new_slots_and_group():
     _full_parity(generate(cfg, seed=31, poison=True), kv_chunk=128)
 
 
+@pytest.mark.parametrize("d,B,L", [(128, 8, 8), (64, 5, 2), (128, 16, 11), (64, 16, 16)],
+                         ids=["64rows", "28rows", "108rows", "128rows"])
+def test_stream_short_pairs(d, B, L):
+    """Ragged batches of short prefixes (empty ones too), where ranges start and
+    end inside the entries that stand for a pair's set-up, for both group sizes
+    of the stream decomposition."""
+    cfg = VerifyConfig(0, "short", "bf16", batch=40, num_q_heads=8, num_kv_heads=2, head_dim=d,
+                       prefix=(0, 700), block_size=B, max_ref=L, vocab=100, qkv_std=0.3,
+                       step_mode="mixed")
+    inp = generate(cfg, seed=300 + B + L, poison=True)
+    out, lse = run_attention(DeviceInputs(inp), -1)
+    ref_out, ref_lse = oracle.verify_attention(inp)
+    check_attention(out, lse, ref_out, ref_lse, "bf16")
+
+
 def test_stream_largest_batch():
     """The stream decomposition at its largest batch (256 sequences): the
     per-sequence tile offsets are scanned over all 256 entries; ragged
