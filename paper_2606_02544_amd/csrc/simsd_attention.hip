@@ -357,7 +357,7 @@ struct KVRing {
 // (measured faster than a deeper one: 3 or 4 tiles cost 13-17 % on the
 // SDAR-8B layer with four whole-tile row waves, 10-35 % with two groups per
 // CU).
-template <int D, int RW, int KW, bool PAGED, bool ROPE>
+template <int D, int RW, int KW, bool PAGED, bool ROPE, bool STREAM>
 __device__ __attribute__((always_inline)) void attend_segment(const AttnArgs& a, const Work& w) {
   constexpr int NW = RW * KW;
   constexpr int NBUF = NW >= 8 ? 4 : 2;
@@ -373,7 +373,15 @@ __device__ __attribute__((always_inline)) void attend_segment(const AttnArgs& a,
   SIMSD_LDS int* s_pg = (SIMSD_LDS int*)(&s_pg_arr[0]);
 
   __syncthreads();                             // the work-group's previous range is done with the LDS
-  const int tid = threadIdx.x, lane = tid & 63;
+  int tid = threadIdx.x;
+  if constexpr (STREAM) {
+    // Opaque per range: the stream kernel's loop would otherwise keep every
+    // lane offset and rotary frequency derived from the thread index in
+    // registers across the ranges, where they spilled.
+    asm volatile("" : "+v"(tid));
+    __builtin_assume(tid >= 0 && tid < NW * 64);
+  }
+  const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // wave-uniform
   const int n = lane & 31, h = lane >> 5;
   const int rw = wave % RW, kw = wave / RW;    // row wave, key half
@@ -714,7 +722,7 @@ template <int D, int RW, int KW, bool PAGED, bool ROPE>
 __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_kernel(AttnArgs a) {
   Work w;
   if (!setup_work(a, w, D)) return;
-  attend_segment<D, RW, KW, PAGED, ROPE>(a, w);
+  attend_segment<D, RW, KW, PAGED, ROPE, false>(a, w);
 }
 
 // Stream decomposition, for large and ragged batches.  The tiles of all
@@ -800,7 +808,7 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
     w.final = t0 == 0 && w.has_new;
     w.part = a.part + (static_cast<int64_t>(g) * 2 + (x == lo ? 0 : 1)) *
                           static_cast<int64_t>(a.rows_pb) * (D + 2);
-    attend_segment<D, RW, KW, PAGED, ROPE>(a, w);
+    attend_segment<D, RW, KW, PAGED, ROPE, true>(a, w);
     x += t1 - t0;
   }
 }
@@ -1294,7 +1302,8 @@ void launch_bf16_variant(const AttnPlan& p, dim3 grid, const AttnArgs& a, hipStr
     const dim3 sg(p.stream_groups);
     switch (p.row_waves) {
       case 2: hipLaunchKernelGGL((attn_bf16_stream<D, 2, 2, PAGED, ROPE>), sg, dim3(256), 0, st, a); break;
-      default: hipLaunchKernelGGL((attn_bf16_stream<D, 4, 2, PAGED, ROPE>), sg, dim3(512), 0, st, a); break;
+      case 4: hipLaunchKernelGGL((attn_bf16_stream<D, 4, 2, PAGED, ROPE>), sg, dim3(512), 0, st, a); break;
+      default: hipLaunchKernelGGL((attn_bf16_stream<D, 8, 1, PAGED, ROPE>), sg, dim3(512), 0, st, a); break;
     }
     return;
   }

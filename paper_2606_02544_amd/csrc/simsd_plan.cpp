@@ -130,17 +130,21 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
   // resident slot, each with an equal share of all tiles (ragged prefixes do
   // not unbalance it).  It is chosen when the chunked grid would take more than
   // one round of resident groups (where ragged prefixes leave slots idle) and
-  // there are at least 8 tiles per group; kv_chunk -1 asks for it at any size.  Workspace: two partial slots per group, then the
-  // per-sequence tile offsets.  (Row blocks of up to 128 rows; the 8-wave
-  // 256-row group keeps the chunks.)
-  const bool can_stream = d->dtype == SIMSD_BF16 && d->batch <= kMaxStreamBatch &&
-                          r.row_waves <= 4;
-  if (d->kv_chunk == kStreamChunk && !can_stream)
+  // there are at least 8 tiles per group; kv_chunk -1 asks for it at any size
+  // (row blocks of up to 128 rows).  Within one round the chunks stay: on equal
+  // prefixes they are faster (SDAR-8B layer 34.0 against 40.1 us), though not
+  // on uneven ones (8 sequences of 1..8192: 53.9 against 39.9 us), and the
+  // lengths are on the device.  Row blocks of 256 rows, 24 sequences of
+  // prefixes 101..6007: 225 us in chunks, 122 us as a stream (rotary and paged
+  // 262 and 140 us); 60 of 101..1000: 95 and 90 us.  Workspace: two partial
+  // slots per group, then the per-sequence tile offsets.
+  const bool can_stream = d->dtype == SIMSD_BF16 && d->batch <= kMaxStreamBatch;
+  if (d->kv_chunk == kStreamChunk && !(can_stream && r.row_waves <= 4))
     return fail(SIMSD_ERR_UNSUPPORTED,
                 "attention: kv_chunk -1 (stream) needs bf16, at most 128 packed rows "
                 "(Hq/Hkv * (B + L)) and batch <= 256");
   if (can_stream && d->kv_chunk <= 0) {
-    // Stream groups: 8 waves (one per CU) for four row waves, else 4 (two per CU).
+    // Stream groups: 8 waves (one per CU) for four or eight row waves, else 4 (two per CU).
     const int64_t groups = r.row_waves >= 4 ? cus : 2 * int64_t{cus};
     const int64_t tiles = r.pairs * (ceil_div(d->max_prefix_len, kTile) + 1);
     if (d->kv_chunk == kStreamChunk || (tiles >= 8 * groups && r.pairs * r.splits > groups)) {
@@ -153,7 +157,8 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
       // rows, paged, rotary, 134 us at 0, 122 at 2, 108 at 4, 98 at 8, 98 at
       // 12, 104 at 16; 64 rows, 81 us at 0, 72 at 2, 71 at 4, 72 at 8, 75 at
       // 16 (two groups per CU: one's set-up runs beside the other's tiles).
-      // 64 sequences with prefixes 512..32768: 820 us at 0, 812 at 4.
+      // 64 sequences with prefixes 512..32768: 820 us at 0, 812 at 4.  256
+      // rows on the first batch: 144 us at 2, 118 at 4 and 6, 122 at 8 and 12.
       r.seg_tiles = r.row_waves >= 4 ? 8 : 4;
       r.workspace = static_cast<size_t>(groups) * 2 * r.part_floats * 4 +
                     static_cast<size_t>(kMaxStreamBatch + 1) * 8;

@@ -190,6 +190,21 @@ def test_stream_short_pairs(d, B, L):
     check_attention(out, lse, ref_out, ref_lse, "bf16")
 
 
+@pytest.mark.parametrize("d,hq,B,L,batch,page,theta", [
+    (128, 32, 32, 32, 34, 0, 0.0), (128, 32, 29, 24, 34, 16, 1e6), (64, 64, 32, 30, 18, 16, 0.0)],
+    ids=["256rows", "212rows-paged-rope", "496rows-paged"])
+def test_stream_whole_row_blocks(d, hq, B, L, batch, page, theta):
+    """Row blocks of more than 128 rows take the stream decomposition by
+    themselves where the chunks would need more than one round of groups."""
+    cfg = VerifyConfig(0, "blocks", "bf16", batch=batch, num_q_heads=hq, num_kv_heads=8, head_dim=d,
+                       prefix=(0, 500), block_size=B, max_ref=L, vocab=100, page_size=page,
+                       qkv_std=0.3, step_mode="mixed")
+    inp = generate(cfg, seed=330 + B + L, poison=True)
+    out, lse = run_attention(DeviceInputs(inp), rope_theta=theta)
+    ref_out, ref_lse = oracle.verify_attention(inp, rope_theta=theta)
+    check_attention(out, lse, ref_out, ref_lse, "bf16")
+
+
 def test_stream_largest_batch():
     """The stream decomposition at its largest batch (256 sequences): the
     per-sequence tile offsets are scanned over all 256 entries; ragged
