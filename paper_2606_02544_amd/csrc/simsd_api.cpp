@@ -178,7 +178,6 @@ extern "C" simsd_status simsd_verify_accept(const simsd_accept_desc* desc, const
     a.draft_prob = draft_prob;
     a.accept_len = accept_len;
     a.part = static_cast<AcceptPartial*>(workspace);
-    a.nvec = p.nvec;
     a.chunk_vecs = p.chunk_vecs;
     a.B = desc->block_size;
     a.L = desc->max_ref;
@@ -293,7 +292,7 @@ extern "C" simsd_status simsd_verify_accept_sampled(
     a.accept_len = accept_len;
     a.correction = correction;
     a.part = static_cast<AcceptPartial*>(workspace);
-    a.nvec = p.nvec;
+    a.draw_nvec = p.draw_nvec;
     a.chunk_vecs = p.chunk_vecs;
     a.B = desc->block_size;
     a.L = desc->max_ref;

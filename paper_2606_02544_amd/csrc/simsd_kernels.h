@@ -46,7 +46,7 @@ struct AcceptArgs {
   float* draft_prob;          // greedy: target probability of each draft; sampled: p_theta(D_r)
   int32_t* accept_len;
   AcceptPartial* part;
-  int64_t nvec, chunk_vecs;
+  int64_t chunk_vecs;
   int B, L, V, cpr;
   int rows;                   // partial rows per sequence: B, or B + L (sampled)
   float cl;                   // log2(e) / temperature
@@ -57,7 +57,7 @@ struct AcceptArgs {
   int32_t* correction;        // token drawn at the first rejection, or -1
   DrawRow* draw_row;          // [batch]
   DrawPartial* draw_part;     // [batch, draw_chunks]
-  int64_t draw_vecs;
+  int64_t draw_nvec, draw_vecs;
   int draw_chunks;
   const float* xdraft;        // LM-head path: the drafted tokens' logits [batch, L]
 };

@@ -219,27 +219,31 @@ simsd_status plan_accept(const simsd_accept_desc* d, int cus, AcceptPlan* p, boo
   const int eb = elem_bytes(d->logits_dtype);
   const int w = 16 / eb;
   r.vec = (d->vocab % w == 0) ? w : 1;
-  r.nvec = ceil_div(d->vocab, r.vec);
+  r.draw_nvec = ceil_div(d->vocab, r.vec);
+  // The workspace is sized for chunks of that vector count.  The scan itself
+  // reads aligned 16-byte vectors whatever the vocabulary (entries outside them
+  // go one to a thread), so it may take fewer chunks: no more than vectors, and
+  // by the library's choice at least a vector per thread.
   const int64_t rows = static_cast<int64_t>(d->batch) * r.rows;
-  int64_t cpr = d->chunks_per_row;
-  if (cpr == 0) {
-    cpr = ceil_div(int64_t{kAcceptPerCU} * cus, rows);
-    const int64_t most = std::max<int64_t>(1, r.nvec / kAcceptThreads);
-    if (cpr > most) cpr = most;
-  }
-  if (cpr > r.nvec) cpr = r.nvec;
-  if (cpr > 65535 * 1024) return fail(SIMSD_ERR_BAD_SHAPE, "accept: chunks_per_row too large");
-  r.cpr = static_cast<int>(cpr);
+  r.nvec = std::max<int64_t>(1, d->vocab / w);
+  auto chunks = [&](int64_t nvec) {
+    const int64_t most = std::max<int64_t>(1, nvec / kAcceptThreads);
+    const int64_t c = d->chunks_per_row ? int64_t{d->chunks_per_row}
+                                        : std::min(ceil_div(int64_t{kAcceptPerCU} * cus, rows), most);
+    return std::min(c, nvec);
+  };
+  if (chunks(r.draw_nvec) > 65535 * 1024) return fail(SIMSD_ERR_BAD_SHAPE, "accept: chunks_per_row too large");
+  r.workspace = static_cast<size_t>(rows) * chunks(r.draw_nvec) * sizeof(AcceptPartial);
+  r.cpr = static_cast<int>(chunks(r.nvec));
   r.chunk_vecs = ceil_div(r.nvec, r.cpr);
-  r.workspace = static_cast<size_t>(rows) * r.cpr * sizeof(AcceptPartial);
   if (sampled) {
     // About kAcceptPerCU draw work-groups per compute unit, each at least one
     // vector per thread.
     int64_t g = ceil_div(int64_t{kAcceptPerCU} * cus, d->batch);
-    const int64_t most = std::max<int64_t>(1, r.nvec / kAcceptThreads);
+    const int64_t most = std::max<int64_t>(1, r.draw_nvec / kAcceptThreads);
     g = std::min<int64_t>(std::min<int64_t>(g, most), kAcceptThreads);
     r.draw_chunks = static_cast<int>(std::max<int64_t>(g, 1));
-    r.draw_vecs = ceil_div(r.nvec, r.draw_chunks);
+    r.draw_vecs = ceil_div(r.draw_nvec, r.draw_chunks);
     r.draw_row_off = (r.workspace + 255) / 256 * 256;
     r.draw_part_off = r.draw_row_off + static_cast<size_t>(d->batch) * sizeof(DrawRow);
     r.workspace = r.draw_part_off + static_cast<size_t>(d->batch) * r.draw_chunks * sizeof(DrawPartial);

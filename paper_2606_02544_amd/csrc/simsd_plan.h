@@ -46,8 +46,9 @@ struct AcceptPlan {
   int64_t draw_vecs = 0;  // sampled: vectors per draw chunk
   size_t draw_row_off = 0;   // sampled: workspace offsets (bytes) of the per-sequence
   size_t draw_part_off = 0;  //   draw rows and of the draw chunk partials
-  int vec = 1;            // elements per vector load (16 bytes), or 1 for the scalar path
-  int64_t nvec = 0;       // vectors per row
+  int vec = 1;            // sampled: elements per load of the draw (16 bytes, or one element)
+  int64_t draw_nvec = 0;  // such loads per row
+  int64_t nvec = 0;       // aligned 16-byte vectors the scan reads of a row, at most
   int cpr = 0;            // chunks (work-groups) per row
   int64_t chunk_vecs = 0; // vectors per chunk
   size_t workspace = 0;
