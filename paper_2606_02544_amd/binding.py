@@ -9,6 +9,7 @@ raises at load time; there is no fallback path.
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from typing import Optional
 
@@ -104,8 +105,8 @@ def _check(status: int):
         raise SimsdError(status, lib().simsd_last_error().decode())
 
 
-def _ptr(t: Optional[torch.Tensor]):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+def _addr(t: Optional[torch.Tensor]):
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(dt: torch.dtype) -> int:
@@ -128,15 +129,26 @@ def _stream_of(stream, device: torch.device):
 # Argument checks.  The C library checks sizes, alignment and the workspace,
 # but it only sees pointers: shapes, dtypes, strides and devices of the
 # tensors are checked here, before any call, and raise ValueError.
+#
+# Each call first asks the short tests (_is, _attention_hkv), which only say
+# whether everything holds: formatting the messages of tests that pass, and
+# walking shapes one by one, took most of a small call's host time.  What they
+# do not accept goes through the checks below, which say what is wrong.
 # ----------------------------------------------------------------------------
 def _need(cond: bool, msg: str):
     if not cond:
         raise ValueError(msg)
 
 
+def _is(t, shape, dtype, device) -> bool:
+    return (t.dtype is dtype and t.shape == shape and t.device == device and t.is_contiguous())
+
+
 def _tensor(name: str, t, shape, dtype=None, device=None):
     """t is a contiguous tensor of the given shape (None entries: any size),
     dtype and device."""
+    if isinstance(t, torch.Tensor) and _is(t, shape, dtype, device):
+        return
     _need(isinstance(t, torch.Tensor), f"{name} must be a torch.Tensor")
     _need(t.dim() == len(shape), f"{name} must have {len(shape)} dimensions, got shape {tuple(t.shape)}")
     for i, n in enumerate(shape):
@@ -206,7 +218,7 @@ class _Workspaces:
             nbytes: int) -> Optional[torch.Tensor]:
         if nbytes == 0:
             return None
-        key = (str(device), int(stream_handle), kind)
+        key = (device, int(stream_handle), kind)
         buf = self._bufs.get(key)
         if buf is None or buf.numel() < nbytes:
             if buf is not None:
@@ -214,6 +226,10 @@ class _Workspaces:
             buf = torch.empty(nbytes, dtype=torch.uint8, device=device)
             self._bufs[key] = buf
         return buf
+
+    def held(self, device: torch.device, stream_handle: int, kind: str) -> Optional[torch.Tensor]:
+        """The buffer held for this stream, whatever its size, or None."""
+        return self._bufs.get((device, stream_handle, kind))
 
     def clear(self):
         self._bufs.clear()
@@ -247,14 +263,6 @@ def accept_workspace_size(desc: AcceptDesc) -> int:
     return int(lib().simsd_verify_accept_workspace_size(ctypes.byref(desc)))
 
 
-def _workspace(workspace, device, stream, kind, nbytes):
-    """The caller's workspace (checked), or a cached one for this stream."""
-    if workspace is None:
-        return WORKSPACES.get(device, stream.cuda_stream, kind, nbytes)
-    _tensor("workspace", workspace, (None,), None, device)
-    return workspace
-
-
 def _nbytes(t: Optional[torch.Tensor]) -> int:
     return 0 if t is None else t.numel() * t.element_size()
 
@@ -284,6 +292,77 @@ def check_attention_tensors(q, k_new, v_new, k_cache, v_cache, block_table, pref
     return hkv
 
 
+def _attention_hkv(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens, step_map,
+                   num_ref, out, lse, block_size, max_ref, max_prefix_len, page_size):
+    """KV heads if every argument passes check_attention_tensors, else None."""
+    try:
+        b, n_new, hq, d = q.shape
+        hkv = k_new.shape[2]
+        dt, dev, new = q.dtype, q.device, (b, n_new, hkv, d)
+        if not ((dt is torch.bfloat16 or dt is torch.float32) and n_new == block_size + max_ref
+                and q.is_contiguous() and _is(k_new, new, dt, dev) and _is(v_new, new, dt, dev)
+                and _is(prefix_lens, (b,), torch.int32, dev)
+                and _is(step_map, (b, block_size), torch.int32, dev)
+                and _is(num_ref, (b,), torch.int32, dev)
+                and (out is None or _is(out, q.shape, dt, dev))
+                and (lse is None or _is(lse, (b, hq, n_new), torch.float32, dev))):
+            return None
+        if max_prefix_len > 0:
+            shape, stride = k_cache.shape, k_cache.stride()
+            if not (k_cache.dtype is dt and v_cache.dtype is dt and k_cache.device == dev
+                    and v_cache.device == dev and v_cache.shape == shape
+                    and v_cache.stride() == stride and len(shape) == 4 and stride[3] == 1
+                    and shape[2] == hkv and shape[3] == d):
+                return None
+            if page_size > 0:
+                pages = block_table.shape
+                if not (shape[1] == page_size and len(pages) == 2
+                        and _is(block_table, (b, pages[1]), torch.int32, dev)
+                        and pages[1] * page_size >= max_prefix_len):
+                    return None
+            elif not (shape[0] == b and shape[1] >= max_prefix_len):
+                return None
+        return hkv
+    except (AttributeError, TypeError, ValueError, IndexError):
+        return None
+
+
+@functools.lru_cache(maxsize=1024)
+def _attn_desc(*fields) -> AttnDesc:
+    """AttnDesc of these field values (read only: calls share it)."""
+    return AttnDesc(*fields)
+
+
+@functools.lru_cache(maxsize=1024)
+def _accept_desc(*fields) -> AcceptDesc:
+    return AcceptDesc(*fields)
+
+
+@functools.lru_cache(maxsize=1024)
+def _lmhead_desc(*fields) -> LmheadDesc:
+    return LmheadDesc(*fields)
+
+
+_NEEDS_WORKSPACE = 5             # SIMSD_ERR_WORKSPACE
+
+
+def _run(fn, head, args, workspace, device, handle, kind, size_of, desc):
+    """fn(*head, *args, workspace, bytes, stream).  Without a caller's workspace
+    the buffer held for this stream is offered as it is; the library refuses one
+    that is too small before it enqueues anything, and only then is the size
+    asked for and the buffer grown."""
+    if workspace is not None:
+        _tensor("workspace", workspace, (None,), None, device)
+        _check(fn(*head, *args, workspace.data_ptr(), _nbytes(workspace), handle))
+        return
+    buf = WORKSPACES.held(device, handle, kind)
+    status = fn(*head, *args, *((None, 0) if buf is None else (buf.data_ptr(), buf.numel())), handle)
+    if status == _NEEDS_WORKSPACE:
+        buf = WORKSPACES.get(device, handle, kind, size_of(desc))
+        status = fn(*head, *args, *((None, 0) if buf is None else (buf.data_ptr(), buf.numel())), handle)
+    _check(status)
+
+
 def verify_attention(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens, step_map,
                      num_ref, *, block_size: int, max_ref: int, max_prefix_len: int,
                      page_size: int = 0, kv_chunk: int = 0, scale: float = 0.0,
@@ -296,29 +375,29 @@ def verify_attention(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens
     Raises ValueError on tensors whose shape, dtype, device or layout does not
     match (before anything is launched), SimsdError if the library rejects
     the call."""
-    hkv = check_attention_tensors(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens,
-                                  step_map, num_ref, out, lse, block_size=block_size,
-                                  max_ref=max_ref, max_prefix_len=max_prefix_len,
-                                  page_size=page_size)
-    if desc is None:
-        desc = attention_desc(q, k_cache if max_prefix_len > 0 else k_new, num_kv_heads=hkv,
-                              block_size=block_size, max_ref=max_ref,
-                              max_prefix_len=max_prefix_len, page_size=page_size,
-                              max_pages_per_seq=(block_table.shape[1]
-                                                 if block_table is not None and page_size > 0
-                                                 else 0),
-                              kv_chunk=kv_chunk, scale=scale, rope_theta=rope_theta)
+    hkv = _attention_hkv(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens, step_map,
+                         num_ref, out, lse, block_size, max_ref, max_prefix_len, page_size)
+    if hkv is None:
+        hkv = check_attention_tensors(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens,
+                                      step_map, num_ref, out, lse, block_size=block_size,
+                                      max_ref=max_ref, max_prefix_len=max_prefix_len,
+                                      page_size=page_size)
+    b, n_new, hq, d = q.shape
     dev = q.device
+    if desc is None:
+        st = (k_cache if max_prefix_len > 0 else k_new).stride()
+        pages = block_table.shape[1] if block_table is not None and page_size > 0 else 0
+        desc = _attn_desc(b, hq, hkv, d, block_size, max_ref, max_prefix_len, page_size, pages,
+                          kv_chunk, st[0], st[1], st[2], scale, _dtype_code(q.dtype), rope_theta)
     if out is None:
-        out = torch.empty(q.shape, dtype=q.dtype, device=dev)
+        out = torch.empty_like(q, memory_format=torch.contiguous_format)
     if lse is None and want_lse:
-        lse = torch.empty((q.shape[0], q.shape[2], q.shape[1]), dtype=torch.float32, device=dev)
-    st = _stream_of(stream, dev)
-    workspace = _workspace(workspace, dev, st, "attn", attention_workspace_size(desc))
-    _check(lib().simsd_verify_attention(
-        ctypes.byref(desc), _ptr(q), _ptr(k_new), _ptr(v_new), _ptr(k_cache), _ptr(v_cache),
-        _ptr(block_table), _ptr(prefix_lens), _ptr(step_map), _ptr(num_ref), _ptr(out),
-        _ptr(lse), _ptr(workspace), _nbytes(workspace), ctypes.c_void_p(st.cuda_stream)))
+        lse = torch.empty((b, hq, n_new), dtype=torch.float32, device=dev)
+    _run(lib().simsd_verify_attention, (ctypes.byref(desc),),
+         (q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), _addr(k_cache), _addr(v_cache),
+          _addr(block_table), prefix_lens.data_ptr(), step_map.data_ptr(), num_ref.data_ptr(),
+          out.data_ptr(), _addr(lse)),
+         workspace, dev, _stream_of(stream, dev).cuda_stream, "attn", attention_workspace_size, desc)
     return out, lse
 
 
@@ -343,32 +422,45 @@ def _check_accept_inputs(logits, draft_ids, step_map, num_ref):
     return b, B, V, draft_ids.shape[1], dev
 
 
+def _accept_inputs(logits, draft_ids, step_map, num_ref):
+    """_check_accept_inputs, by the short tests where they hold."""
+    try:
+        b, B, V = logits.shape
+        dt, dev, L = logits.dtype, logits.device, draft_ids.shape[1]
+        if ((dt is torch.bfloat16 or dt is torch.float32) and logits.is_contiguous()
+                and _is(draft_ids, (b, L), torch.int32, dev)
+                and _is(step_map, (b, B), torch.int32, dev) and _is(num_ref, (b,), torch.int32, dev)):
+            return b, B, V, L, dev
+    except (AttributeError, TypeError, ValueError, IndexError):
+        pass
+    return _check_accept_inputs(logits, draft_ids, step_map, num_ref)
+
+
+def _given(name, t, shape, dtype, device):
+    """An output: the caller's tensor (checked), or a new one."""
+    if t is None:
+        return torch.empty(shape, dtype=dtype, device=device)
+    _tensor(name, t, shape, dtype, device)
+    return t
+
+
 def verify_accept(logits, draft_ids, step_map, num_ref, *, chunks_per_row: int = 0,
                   target_ids=None, confidence=None, draft_prob=None, accept_len=None,
                   workspace=None, stream=None, desc: Optional[AcceptDesc] = None):
     """simsd_verify_accept on torch tensors.
     Returns (target_ids, confidence, draft_prob, accept_len)."""
-    b, B, V, L, dev = _check_accept_inputs(logits, draft_ids, step_map, num_ref)
-    _out("target_ids", target_ids, (b, B), torch.int32, dev)
-    _out("confidence", confidence, (b, B), torch.float32, dev)
-    _out("draft_prob", draft_prob, (b, L), torch.float32, dev)
-    _out("accept_len", accept_len, (b,), torch.int32, dev)
+    b, B, V, L, dev = _accept_inputs(logits, draft_ids, step_map, num_ref)
+    target_ids = _given("target_ids", target_ids, (b, B), torch.int32, dev)
+    confidence = _given("confidence", confidence, (b, B), torch.float32, dev)
+    draft_prob = _given("draft_prob", draft_prob, (b, L), torch.float32, dev)
+    accept_len = _given("accept_len", accept_len, (b,), torch.int32, dev)
     if desc is None:
-        desc = accept_desc(logits, L, chunks_per_row)
-    if target_ids is None:
-        target_ids = torch.empty((b, B), dtype=torch.int32, device=dev)
-    if confidence is None:
-        confidence = torch.empty((b, B), dtype=torch.float32, device=dev)
-    if draft_prob is None:
-        draft_prob = torch.empty((b, L), dtype=torch.float32, device=dev)
-    if accept_len is None:
-        accept_len = torch.empty((b,), dtype=torch.int32, device=dev)
-    st = _stream_of(stream, dev)
-    workspace = _workspace(workspace, dev, st, "accept", accept_workspace_size(desc))
-    _check(lib().simsd_verify_accept(
-        ctypes.byref(desc), _ptr(logits), _ptr(draft_ids), _ptr(step_map), _ptr(num_ref),
-        _ptr(target_ids), _ptr(confidence), _ptr(draft_prob), _ptr(accept_len),
-        _ptr(workspace), _nbytes(workspace), ctypes.c_void_p(st.cuda_stream)))
+        desc = _accept_desc(b, B, L, V, chunks_per_row, _dtype_code(logits.dtype))
+    _run(lib().simsd_verify_accept, (ctypes.byref(desc),),
+         (logits.data_ptr(), draft_ids.data_ptr(), step_map.data_ptr(), num_ref.data_ptr(),
+          target_ids.data_ptr(), confidence.data_ptr(), draft_prob.data_ptr(),
+          accept_len.data_ptr()),
+         workspace, dev, _stream_of(stream, dev).cuda_stream, "accept", accept_workspace_size, desc)
     return target_ids, confidence, draft_prob, accept_len
 
 
@@ -382,25 +474,16 @@ def verify_accept_noalloc(logits, draft_ids, step_map, num_ref, *, target_ids=No
     cannot allocate; pass preallocated outputs to allocate nothing at all).
     Calls overlapping on one GPU race on that scratch.
     Returns (target_ids, confidence, draft_prob, accept_len)."""
-    b, B, V, L, dev = _check_accept_inputs(logits, draft_ids, step_map, num_ref)
-    _out("target_ids", target_ids, (b, B), torch.int32, dev)
-    _out("confidence", confidence, (b, B), torch.float32, dev)
-    _out("draft_prob", draft_prob, (b, L), torch.float32, dev)
-    _out("accept_len", accept_len, (b,), torch.int32, dev)
-    desc = accept_desc(logits, L)
-    if target_ids is None:
-        target_ids = torch.empty((b, B), dtype=torch.int32, device=dev)
-    if confidence is None:
-        confidence = torch.empty((b, B), dtype=torch.float32, device=dev)
-    if draft_prob is None:
-        draft_prob = torch.empty((b, L), dtype=torch.float32, device=dev)
-    if accept_len is None:
-        accept_len = torch.empty((b,), dtype=torch.int32, device=dev)
-    st = _stream_of(stream, dev)
+    b, B, V, L, dev = _accept_inputs(logits, draft_ids, step_map, num_ref)
+    target_ids = _given("target_ids", target_ids, (b, B), torch.int32, dev)
+    confidence = _given("confidence", confidence, (b, B), torch.float32, dev)
+    draft_prob = _given("draft_prob", draft_prob, (b, L), torch.float32, dev)
+    accept_len = _given("accept_len", accept_len, (b,), torch.int32, dev)
+    desc = _accept_desc(b, B, L, V, 0, _dtype_code(logits.dtype))
     _check(lib().simsd_verify_accept_noalloc(
-        ctypes.byref(desc), _ptr(logits), _ptr(draft_ids), _ptr(step_map), _ptr(num_ref),
-        _ptr(target_ids), _ptr(confidence), _ptr(draft_prob), _ptr(accept_len),
-        ctypes.c_void_p(st.cuda_stream)))
+        ctypes.byref(desc), logits.data_ptr(), draft_ids.data_ptr(), step_map.data_ptr(),
+        num_ref.data_ptr(), target_ids.data_ptr(), confidence.data_ptr(), draft_prob.data_ptr(),
+        accept_len.data_ptr(), _stream_of(stream, dev).cuda_stream))
     return target_ids, confidence, draft_prob, accept_len
 
 
@@ -414,31 +497,21 @@ def verify_accept_sampled(logits, draft_logits, draft_ids, step_map, num_ref, un
                           stream=None, desc: Optional[AcceptDesc] = None):
     """simsd_verify_accept_sampled on torch tensors.
     Returns (p_target, p_draft, accept_len, correction)."""
-    b, B, V, L, dev = _check_accept_inputs(logits, draft_ids, step_map, num_ref)
+    b, B, V, L, dev = _accept_inputs(logits, draft_ids, step_map, num_ref)
     _tensor("draft_logits", draft_logits, (b, L, V), logits.dtype, dev)
     _tensor("uniforms", uniforms, (b, L + 1), torch.float32, dev)
-    _out("p_target", p_target, (b, L), torch.float32, dev)
-    _out("p_draft", p_draft, (b, L), torch.float32, dev)
-    _out("accept_len", accept_len, (b,), torch.int32, dev)
-    _out("correction", correction, (b,), torch.int32, dev)
+    p_target = _given("p_target", p_target, (b, L), torch.float32, dev)
+    p_draft = _given("p_draft", p_draft, (b, L), torch.float32, dev)
+    accept_len = _given("accept_len", accept_len, (b,), torch.int32, dev)
+    correction = _given("correction", correction, (b,), torch.int32, dev)
     if desc is None:
-        desc = accept_desc(logits, L, chunks_per_row)
-    if p_target is None:
-        p_target = torch.empty((b, L), dtype=torch.float32, device=dev)
-    if p_draft is None:
-        p_draft = torch.empty((b, L), dtype=torch.float32, device=dev)
-    if accept_len is None:
-        accept_len = torch.empty((b,), dtype=torch.int32, device=dev)
-    if correction is None:
-        correction = torch.empty((b,), dtype=torch.int32, device=dev)
-    st = _stream_of(stream, dev)
-    workspace = _workspace(workspace, dev, st, "accept_sampled",
-                           accept_sampled_workspace_size(desc))
-    _check(lib().simsd_verify_accept_sampled(
-        ctypes.byref(desc), ctypes.c_float(temperature), _ptr(logits), _ptr(draft_logits),
-        _ptr(draft_ids), _ptr(step_map), _ptr(num_ref), _ptr(uniforms), _ptr(p_target),
-        _ptr(p_draft), _ptr(accept_len), _ptr(correction), _ptr(workspace),
-        _nbytes(workspace), ctypes.c_void_p(st.cuda_stream)))
+        desc = _accept_desc(b, B, L, V, chunks_per_row, _dtype_code(logits.dtype))
+    _run(lib().simsd_verify_accept_sampled, (ctypes.byref(desc), temperature),
+         (logits.data_ptr(), draft_logits.data_ptr(), draft_ids.data_ptr(), step_map.data_ptr(),
+          num_ref.data_ptr(), uniforms.data_ptr(), p_target.data_ptr(), p_draft.data_ptr(),
+          accept_len.data_ptr(), correction.data_ptr()),
+         workspace, dev, _stream_of(stream, dev).cuda_stream, "accept_sampled",
+         accept_sampled_workspace_size, desc)
     return p_target, p_draft, accept_len, correction
 
 
@@ -452,11 +525,7 @@ def lmhead_workspace_size(desc: LmheadDesc) -> int:
     return int(lib().simsd_verify_accept_lmhead_workspace_size(ctypes.byref(desc)))
 
 
-def verify_accept_lmhead(hidden, weight, draft_ids, step_map, num_ref, *, target_ids=None,
-                         confidence=None, draft_prob=None, accept_len=None, workspace=None,
-                         stream=None, desc: Optional[LmheadDesc] = None):
-    """simsd_verify_accept_lmhead on torch tensors (hidden [b, B, H], weight [V, H]).
-    Returns (target_ids, confidence, draft_prob, accept_len)."""
+def _check_lmhead_inputs(hidden, weight, draft_ids, step_map, num_ref):
     _need(isinstance(hidden, torch.Tensor) and hidden.dim() == 3,
           "hidden must be a 3-D tensor [batch, B, H]")
     b, B, H = hidden.shape
@@ -470,27 +539,40 @@ def verify_accept_lmhead(hidden, weight, draft_ids, step_map, num_ref, *, target
     _int32("draft_ids", draft_ids, (b, None), dev)
     _int32("step_map", step_map, (b, B), dev)
     _int32("num_ref", num_ref, (b,), dev)
-    L = draft_ids.shape[1]
-    _out("target_ids", target_ids, (b, B), torch.int32, dev)
-    _out("confidence", confidence, (b, B), torch.float32, dev)
-    _out("draft_prob", draft_prob, (b, L), torch.float32, dev)
-    _out("accept_len", accept_len, (b,), torch.int32, dev)
+    return b, B, H, V, draft_ids.shape[1], dev
+
+
+def _lmhead_inputs(hidden, weight, draft_ids, step_map, num_ref):
+    """_check_lmhead_inputs, by the short tests where they hold."""
+    try:
+        b, B, H = hidden.shape
+        V, L, dev = weight.shape[0], draft_ids.shape[1], hidden.device
+        if (_is(hidden, (b, B, H), torch.bfloat16, dev) and _is(weight, (V, H), torch.bfloat16, dev)
+                and _is(draft_ids, (b, L), torch.int32, dev)
+                and _is(step_map, (b, B), torch.int32, dev) and _is(num_ref, (b,), torch.int32, dev)):
+            return b, B, H, V, L, dev
+    except (AttributeError, TypeError, ValueError, IndexError):
+        pass
+    return _check_lmhead_inputs(hidden, weight, draft_ids, step_map, num_ref)
+
+
+def verify_accept_lmhead(hidden, weight, draft_ids, step_map, num_ref, *, target_ids=None,
+                         confidence=None, draft_prob=None, accept_len=None, workspace=None,
+                         stream=None, desc: Optional[LmheadDesc] = None):
+    """simsd_verify_accept_lmhead on torch tensors (hidden [b, B, H], weight [V, H]).
+    Returns (target_ids, confidence, draft_prob, accept_len)."""
+    b, B, H, V, L, dev = _lmhead_inputs(hidden, weight, draft_ids, step_map, num_ref)
+    target_ids = _given("target_ids", target_ids, (b, B), torch.int32, dev)
+    confidence = _given("confidence", confidence, (b, B), torch.float32, dev)
+    draft_prob = _given("draft_prob", draft_prob, (b, L), torch.float32, dev)
+    accept_len = _given("accept_len", accept_len, (b,), torch.int32, dev)
     if desc is None:
-        desc = lmhead_desc(hidden, weight, L)
-    if target_ids is None:
-        target_ids = torch.empty((b, B), dtype=torch.int32, device=dev)
-    if confidence is None:
-        confidence = torch.empty((b, B), dtype=torch.float32, device=dev)
-    if draft_prob is None:
-        draft_prob = torch.empty((b, L), dtype=torch.float32, device=dev)
-    if accept_len is None:
-        accept_len = torch.empty((b,), dtype=torch.int32, device=dev)
-    st = _stream_of(stream, dev)
-    workspace = _workspace(workspace, dev, st, "lmhead", lmhead_workspace_size(desc))
-    _check(lib().simsd_verify_accept_lmhead(
-        ctypes.byref(desc), _ptr(hidden), _ptr(weight), _ptr(draft_ids), _ptr(step_map),
-        _ptr(num_ref), _ptr(target_ids), _ptr(confidence), _ptr(draft_prob), _ptr(accept_len),
-        _ptr(workspace), _nbytes(workspace), ctypes.c_void_p(st.cuda_stream)))
+        desc = _lmhead_desc(b, B, L, V, H, _dtype_code(hidden.dtype))
+    _run(lib().simsd_verify_accept_lmhead, (ctypes.byref(desc),),
+         (hidden.data_ptr(), weight.data_ptr(), draft_ids.data_ptr(), step_map.data_ptr(),
+          num_ref.data_ptr(), target_ids.data_ptr(), confidence.data_ptr(), draft_prob.data_ptr(),
+          accept_len.data_ptr()),
+         workspace, dev, _stream_of(stream, dev).cuda_stream, "lmhead", lmhead_workspace_size, desc)
     return target_ids, confidence, draft_prob, accept_len
 
 
