@@ -13,8 +13,8 @@
 // (one wave per row) and finalize_kernel (simsd_accept.hip) finds the accepted
 // prefix from them as for stored logits.
 //
-// Tiles: TR rows x TV vocabulary entries per work-group of WV x WR waves (4 x 2
-// in every variant); wave w covers rows (TR/WR)*(w/WV).. and vocabulary
+// Tiles: TR rows x TV vocabulary entries per work-group of WV x WR waves (4 x 1
+// for 32 rows, else 4 x 2); wave w covers rows (TR/WR)*(w/WV).. and vocabulary
 // (TV/WV)*(w%WV).. in 32 x 32 MFMA blocks.  The reduction dimension streams in
 // KS-wide stages through a ring of NBUF LDS stages filled by direct
 // global-to-LDS loads, so several stages are in flight without staging
@@ -36,6 +36,7 @@ constexpr int kNoIndex = 0x7fffffff;
 constexpr int NT = 512;                  // threads of the merge kernel
 // Row-count thresholds of the variants (see launch_lmhead_scan).
 constexpr int kFewRows = 32;
+constexpr int kHalfTileRows = 64;
 constexpr int kOneTileRows = 128;
 
 #define LM_LDS __attribute__((address_space(3)))
@@ -356,14 +357,20 @@ hipError_t launch_variant(const LmheadArgs& a, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_lmhead_scan(const LmheadArgs& a, hipStream_t st) {
-  // Few rows: the weight stream is all there is; 128-entry vocabulary tiles
-  // (more, shorter work-groups) and 54 KB of LDS, two work-groups per CU.  Up
-  // to one row tile: 128-byte row segments, one work-group per CU, and the
-  // weight (read by no other work-group) streamed past the L2 so that the
-  // L2 keeps the hidden rows every work-group re-reads.  More rows: 256-row
-  // tiles halve the weight re-reads and the LDS reads per MFMA; the two row
-  // tiles of a vocabulary tile share its weight lines through the L2.
-  if (a.R <= kFewRows) return launch_variant<128, 128, 32, 3>(a, st);
+  // Up to one row tile the weight stream is all the work: it is read by no
+  // other work-group, so it goes past the L2, which keeps the hidden rows that
+  // every work-group re-reads.  Row tiles of 32, 64 and 128 rows, so that few
+  // rows do not load and multiply a large tile's padding.  32 rows: 128-entry
+  // vocabulary tiles (more, shorter work-groups), 62 KB of LDS, two work-groups
+  // per CU.  More: 128-byte row segments (64-byte ones fetch each line twice:
+  // 370 us at 64 rows, 404 us at 128), one work-group per CU.  Scan kernel,
+  // V = 151936: R = 4, H = 2048: 117 us, 5.3 TB/s (144 us with a 128-row tile);
+  // H = 4096: R = 32 191 us (266), R = 64 228 us (265), R = 128 281 us.
+  // More rows: 256-row tiles halve the weight re-reads and the LDS reads per
+  // MFMA; the two row tiles of a vocabulary tile share its weight lines through
+  // the L2.
+  if (a.R <= kFewRows) return launch_variant<32, 128, 64, 3, 4, 1, true>(a, st);
+  if (a.R <= kHalfTileRows) return launch_variant<64, 256, 64, 3, 4, 2, true>(a, st);
   if (a.R <= kOneTileRows) return launch_variant<128, 256, 64, 3, 4, 2, true>(a, st);
   return launch_variant<256, 256, 64, 2>(a, st);
 }
