@@ -175,6 +175,21 @@ def test_max_new_slots_and_group():
     _full_parity(generate(cfg, seed=31, poison=True), kv_chunk=128)
 
 
+@pytest.mark.parametrize("dtype,d,B,L,top", [
+    ("bf16", 128, 5, 3, 330), ("bf16", 128, 16, 16, 1030), ("bf16", 64, 8, 8, 4200),
+    ("f32", 128, 4, 4, 1030), ("f32", 64, 9, 9, 4200)])
+def test_merge_of_many_splits(dtype, d, B, L, top):
+    """Merges whose waves share 5 to 66 splits (one round and several; sequences
+    of one split and of none beside them), rows that do not fill a work-group."""
+    cfg = VerifyConfig(0, "merge", dtype, batch=7, num_q_heads=6, num_kv_heads=2, head_dim=d,
+                       prefix=(0, top), block_size=B, max_ref=L, vocab=100,
+                       qkv_std=0.3 if dtype == "bf16" else 1.0, step_mode="mixed")
+    inp = generate(cfg, seed=350 + B + top, poison=True)
+    out, lse = run_attention(DeviceInputs(inp), 64)
+    ref_out, ref_lse = oracle.verify_attention(inp)
+    check_attention(out, lse, ref_out, ref_lse, dtype)
+
+
 @pytest.mark.parametrize("d,B,L", [(128, 8, 8), (64, 5, 2), (128, 16, 11), (64, 16, 16)],
                          ids=["64rows", "28rows", "108rows", "128rows"])
 def test_stream_short_pairs(d, B, L):
