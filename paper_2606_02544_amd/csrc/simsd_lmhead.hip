@@ -38,6 +38,7 @@ constexpr int NT = 512;                  // threads of the merge kernel
 constexpr int kFewRows = 32;
 constexpr int kHalfTileRows = 64;
 constexpr int kOneTileRows = 128;
+constexpr int kThreeQuarterRows = 192;
 
 #define LM_LDS __attribute__((address_space(3)))
 
@@ -359,19 +360,21 @@ hipError_t launch_variant(const LmheadArgs& a, hipStream_t st) {
 hipError_t launch_lmhead_scan(const LmheadArgs& a, hipStream_t st) {
   // Up to one row tile the weight stream is all the work: it is read by no
   // other work-group, so it goes past the L2, which keeps the hidden rows that
-  // every work-group re-reads.  Row tiles of 32, 64 and 128 rows, so that few
+  // every work-group re-reads.  Row tiles of 32, 64, 128 and 192 rows, so that few
   // rows do not load and multiply a large tile's padding.  32 rows: 128-entry
   // vocabulary tiles (more, shorter work-groups), 62 KB of LDS, two work-groups
   // per CU.  More: 128-byte row segments (64-byte ones fetch each line twice:
   // 370 us at 64 rows, 404 us at 128), one work-group per CU.  Scan kernel,
   // V = 151936: R = 4, H = 2048: 117 us, 5.3 TB/s (144 us with a 128-row tile);
-  // H = 4096: R = 32 191 us (266), R = 64 228 us (265), R = 128 281 us.
+  // H = 4096: R = 32 191 us (266), R = 64 228 us (265), R = 128 281 us; R = 192
+  // 349 us (392 with a 256-row tile), R = 160 342 us (390), two stages deep.
   // More rows: 256-row tiles halve the weight re-reads and the LDS reads per
   // MFMA; the two row tiles of a vocabulary tile share its weight lines through
   // the L2.
   if (a.R <= kFewRows) return launch_variant<32, 128, 64, 3, 4, 1, true>(a, st);
   if (a.R <= kHalfTileRows) return launch_variant<64, 256, 64, 3, 4, 2, true>(a, st);
   if (a.R <= kOneTileRows) return launch_variant<128, 256, 64, 3, 4, 2, true>(a, st);
+  if (a.R <= kThreeQuarterRows) return launch_variant<192, 256, 64, 2, 4, 2, true>(a, st);
   return launch_variant<256, 256, 64, 2>(a, st);
 }
 

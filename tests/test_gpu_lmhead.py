@@ -73,12 +73,13 @@ def test_lmhead_parity(case):
     check_lmhead(inp, hidden, weight, run_lmhead(inp, hidden, weight))
 
 
-@pytest.mark.parametrize("b,B", [(1, 1), (1, 31), (2, 16), (3, 11), (3, 21), (4, 16), (5, 13)],
+@pytest.mark.parametrize("b,B", [(1, 1), (1, 31), (2, 16), (3, 11), (3, 21), (4, 16), (5, 13), (3, 43),
+                                 (3, 64), (4, 49)],
                          ids=lambda x: str(x))
 @pytest.mark.parametrize("V,H", [(1, 64), (127, 128), (1100, 192), (2049, 448)])
 def test_lmhead_row_tile_edges(b, B, V, H):
-    """Row counts around the 32-, 64- and 128-row tiles (1, 31, 32, 33, 63, 64,
-    65), with one to seven stages of the reduction dimension and ragged
+    """Row counts around the 32-, 64-, 128- and 192-row tiles (1, 31, 32, 33, 63,
+    64, 65, 129, 192, 196), with one to seven stages of the reduction dimension and ragged
     vocabularies."""
     cfg = VerifyConfig(0, "lmhead", "bf16", batch=b, num_q_heads=2, num_kv_heads=1, head_dim=64,
                        prefix=4, block_size=B, max_ref=B, vocab=V, plant=0.6, step_mode="mixed")
