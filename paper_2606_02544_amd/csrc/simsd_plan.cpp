@@ -99,11 +99,19 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     r.waves = r.row_waves <= 2 ? 2 * r.row_waves : r.row_waves;
     r.rows_pb = r.row_waves * 32;
   } else {
-    // One or two 16-row blocks per work-group, whose four waves split the
-    // keys; two groups per CU.
+    // One or two 16-row blocks per work-group, whose four waves split the keys;
+    // two groups per CU.  Two blocks read K and V half as often, but small
+    // problems want the shorter work-groups: one block while there are fewer
+    // than six 64-key pieces of 32-row blocks per CU.  Call in a graph, 32/8
+    // heads, D 128, 16 new slots, two blocks -> one: 1 sequence of 256 keys
+    // (64 pieces) 13.8 -> 10.5 us, of 4096 (1024) 29.2 -> 23.5, of 16000 (4000)
+    // 58.2 -> 60.3; 4 of 1024 (1024) 29.1 -> 24.7, 8 of 1024 (2048)
+    // 39.4 -> 47.8 us.
     r.waves = 4;
     r.row_waves = 4;
-    r.rows_pb = r.rows <= 16 ? 16 : 32;
+    const int64_t pieces = static_cast<int64_t>(d->batch) * d->num_kv_heads * ceil_div(r.rows, 32) *
+                           ceil_div(d->max_prefix_len, kTile);
+    r.rows_pb = r.rows <= 16 || pieces < 6 * int64_t{cus} ? 16 : 32;
   }
   r.row_blocks = static_cast<int>(ceil_div(r.rows, r.rows_pb));
   if (static_cast<int64_t>(d->num_kv_heads) * r.row_blocks > 65535)

@@ -13,7 +13,7 @@ from synth import VerifyConfig, generate
 pytestmark = pytest.mark.gpu
 
 CASES = [
-    # head_dim, Hq, Hkv, B, L, prefix, page, kv_chunk, theta
+    # head_dim, Hq, Hkv, B, L, prefix, page, kv_chunk, theta (small: 16-row work-groups)
     (128, 1, 1, 1, 0, (1, 1), 0, 0, 0.0),          # one row, one key: three waves idle
     (128, 2, 1, 4, 4, (15, 17), 0, 0, 0.0),        # 16 rows; around one sub-tile
     (128, 4, 2, 8, 1, (63, 65), 16, 0, 0.0),       # 18 rows: two blocks, around a chunk
@@ -25,12 +25,19 @@ CASES = [
     (64, 12, 2, 17, 16, (5, 333), 8, 64, 1e4),     # rotary: slots shared by two row blocks
     (128, 3, 1, 32, 32, (0, 90), 0, 0, 1e6),       # rotary: 64 rotated keys, 192 rows
 ]
+# The same with enough sequences for 32-row work-groups.
+LARGE = [
+    (128, 16, 8, 9, 1, (0, 900), 0, 0, 0.0),       # 20 rows: the second block partial
+    (64, 16, 8, 8, 8, (700, 900), 16, 0, 0.0),     # 32 rows exactly, paged
+    (128, 24, 8, 8, 7, (0, 450), 5, 0, 1e6),       # 45 rows: a second, partial group; rotary
+    (64, 32, 8, 11, 11, (0, 450), 0, 64, 1e4),     # 88 rows, 64-key splits, rotary
+]
 
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("case", CASES + LARGE, ids=lambda c: "-".join(map(str, c)))
 def test_f32_tiles(case):
     d, hq, hkv, B, L, prefix, page, kv_chunk, theta = case
-    cfg = VerifyConfig(0, "f32", "f32", batch=4, num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
+    cfg = VerifyConfig(0, "f32", "f32", batch=16 if case in LARGE else 4, num_q_heads=hq, num_kv_heads=hkv, head_dim=d,
                        prefix=prefix, block_size=B, max_ref=L, vocab=100, page_size=page,
                        qkv_std=1.0, step_mode="mixed" if L else "full")
     inp = generate(cfg, seed=500 + d + B, poison=True)
