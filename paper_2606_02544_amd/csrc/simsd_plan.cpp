@@ -110,7 +110,7 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     r.waves = 4;
     r.row_waves = 4;
     const int64_t pieces = static_cast<int64_t>(d->batch) * d->num_kv_heads * ceil_div(r.rows, 32) *
-                           ceil_div(d->max_prefix_len, kTile);
+                           std::max<int64_t>(1, ceil_div(d->max_prefix_len, kTile));
     r.rows_pb = r.rows <= 16 || pieces < 6 * int64_t{cus} ? 16 : 32;
   }
   r.row_blocks = static_cast<int>(ceil_div(r.rows, r.rows_pb));
