@@ -347,6 +347,13 @@ struct KVRing {
   }
 };
 
+// Partials of the stream decomposition are fp32 for 256-row blocks: pairs that
+// the chunks would finish whole in fp32 may be cut there, and a bf16 partial
+// would add a rounding (17 sequences of 900..1100, RMS error against 64 bits:
+// 1.47e-4 with bf16 partials, 1.20e-4 whole and with fp32 ones).
+template <bool STREAM, int RW>
+constexpr bool kF32Partial = STREAM && RW == 8;
+
 // RW row waves of 32 rows each; KW = 2 pairs every row wave with a second wave
 // that takes the other 32-key half of each tile (the stream decomposition and
 // row blocks of up to 64 rows, where the extra waves double the work in
@@ -695,19 +702,29 @@ __device__ __attribute__((always_inline)) void attend_segment(const AttnArgs& a,
         a.lse[(static_cast<int64_t>(w.b) * a.hq + hq) * a.n_new + t] =
             valid ? (m_run + __log2f(l_tot)) * kLn2 : kNegInf;
     } else {
-      // bf16 partial: this range's output normalised by its own sum (so in
-      // the range of V), rounded to bf16; the max and the sum stay fp32.
       float* part = w.part;
-      uint16_t* prow = reinterpret_cast<uint16_t*>(part) + rowl * D;
-      const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+      if constexpr (kF32Partial<STREAM, RW>) {
+        // fp32 partial, not normalised.
 #pragma unroll
-      for (int c = 0; c < NB; ++c)
+        for (int c = 0; c < NB; ++c)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const u32x2 v = {pack2(o[c][4 * q] * inv, o[c][4 * q + 1] * inv),
-                           pack2(o[c][4 * q + 2] * inv, o[c][4 * q + 3] * inv)};
-          *reinterpret_cast<u32x2*>(prow + 32 * c + 8 * q + 4 * h) = v;
-        }
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(part + rowl * D + 32 * c + 8 * q + 4 * h) =
+                f32x4{o[c][4 * q], o[c][4 * q + 1], o[c][4 * q + 2], o[c][4 * q + 3]};
+      } else {
+        // bf16 partial: this range's output normalised by its own sum (so in
+        // the range of V), rounded to bf16; the max and the sum stay fp32.
+        uint16_t* prow = reinterpret_cast<uint16_t*>(part) + rowl * D;
+        const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
+#pragma unroll
+        for (int c = 0; c < NB; ++c)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const u32x2 v = {pack2(o[c][4 * q] * inv, o[c][4 * q + 1] * inv),
+                             pack2(o[c][4 * q + 2] * inv, o[c][4 * q + 3] * inv)};
+            *reinterpret_cast<u32x2*>(prow + 32 * c + 8 * q + 4 * h) = v;
+          }
+      }
       if (h == 0) {
         part[a.rows_pb * D + rowl] = m_run;
         part[a.rows_pb * D + a.rows_pb + rowl] = l_tot;
@@ -1157,9 +1174,9 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
 // range was written whole by that group.
 // SB partials are loaded per round (indices clamped, so a round always loads
 // SB); the launcher takes SB near the split count.
-template <int D, typename OutT, bool STREAM, int SB>
+template <int D, typename OutT, bool STREAM, int SB, typename PartT = OutT>
 __global__ void __launch_bounds__(256) merge_kernel(AttnArgs a) {
-  constexpr int DPT = 16 / static_cast<int>(sizeof(OutT));    // dims per thread
+  constexpr int DPT = 16 / static_cast<int>(sizeof(PartT));   // dims per thread
   constexpr int TPR = D / DPT;                                // threads per row
   // A zero the compiler cannot see through: keeps the per-sequence reads
   // vector loads issued with the others instead of late scalar loads.
@@ -1219,7 +1236,7 @@ __global__ void __launch_bounds__(256) merge_kernel(AttnArgs a) {
       const float* ps = part_of(s0 + s);
       mv[s] = ps[mo + rl];
       lv[s] = ps[mo + a.rows_pb + rl];
-      if constexpr (sizeof(OutT) == 2) {   // bf16 partials, normalised by their sum
+      if constexpr (sizeof(PartT) == 2) {   // bf16 partials, normalised by their sum
         const u32x4 w4 = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint16_t*>(ps) + rl * D + d0);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1262,7 +1279,7 @@ __global__ void __launch_bounds__(256) merge_kernel(AttnArgs a) {
         const float wt = __builtin_amdgcn_exp2f(mv[s] - mn);
         lsum += wt * lv[s];
         // bf16 partials hold O / l: their weight carries the sum.
-        const float wo = sizeof(OutT) == 2 ? wt * lv[s] : wt;
+        const float wo = sizeof(PartT) == 2 ? wt * lv[s] : wt;
 #pragma unroll
         for (int e = 0; e < DPT; ++e) acc[e] += wo * ov[s][e];
       }
@@ -1272,10 +1289,13 @@ __global__ void __launch_bounds__(256) merge_kernel(AttnArgs a) {
   const bool ok = valid && lsum > 0.f;
   const float inv = ok ? 1.f / lsum : 0.f;
   const int64_t orow = ((static_cast<int64_t>(b) * a.n_new + t) * a.hq + hq) * D + d0;
-  if constexpr (sizeof(OutT) == 2) {
+  if constexpr (DPT == 8) {
     const u32x4 pk = {pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv),
                       pack2(acc[4] * inv, acc[5] * inv), pack2(acc[6] * inv, acc[7] * inv)};
     *reinterpret_cast<u32x4*>(static_cast<uint16_t*>(a.out) + orow) = pk;
+  } else if constexpr (sizeof(OutT) == 2) {
+    const u32x2 pk = {pack2(acc[0] * inv, acc[1] * inv), pack2(acc[2] * inv, acc[3] * inv)};
+    *reinterpret_cast<u32x2*>(static_cast<uint16_t*>(a.out) + orow) = pk;
   } else {
     *reinterpret_cast<f32x4*>(static_cast<float*>(a.out) + orow) =
         f32x4{acc[0] * inv, acc[1] * inv, acc[2] * inv, acc[3] * inv};
@@ -1453,6 +1473,17 @@ void launch_merge(int splits, int rows, dim3 grid, const AttnArgs& a, hipStream_
   else hipLaunchKernelGGL((merge_wide_kernel<D, OutT, 8>), grid, dim3(256), 0, st, a);
 }
 
+template <int D>
+void launch_stream_merge(int row_waves, int rows, dim3 grid, const AttnArgs& a, hipStream_t st) {
+  if (row_waves == 8) {
+    grid.x = (rows * D / 4 + 255) / 256;
+    hipLaunchKernelGGL((merge_kernel<D, uint16_t, true, 4, float>), grid, dim3(256), 0, st, a);
+  } else {
+    grid.x = (rows * D / 8 + 255) / 256;
+    hipLaunchKernelGGL((merge_kernel<D, uint16_t, true, 4>), grid, dim3(256), 0, st, a);
+  }
+}
+
 template <int D, bool PAGED, bool ROPE>
 void launch_f32_rows(const AttnPlan& p, dim3 grid, const AttnArgs& a, hipStream_t st) {
   switch (p.rows_pb) {
@@ -1499,9 +1530,8 @@ hipError_t launch_attention(const simsd_attn_desc& d, const AttnPlan& p, const A
   if (p.stream) {
     // A pair meets a few group ranges (two or three on the ragged batches);
     // more take further rounds.
-    mgrid.x = (rows * d.head_dim / 8 + 255) / 256;
-    if (d.head_dim == 128) hipLaunchKernelGGL((merge_kernel<128, uint16_t, true, 4>), mgrid, dim3(256), 0, st, a);
-    else hipLaunchKernelGGL((merge_kernel<64, uint16_t, true, 4>), mgrid, dim3(256), 0, st, a);
+    if (d.head_dim == 128) launch_stream_merge<128>(p.row_waves, rows, mgrid, a, st);
+    else launch_stream_merge<64>(p.row_waves, rows, mgrid, a, st);
   } else if (d.head_dim == 128) {
     if (bf16) launch_merge<128, uint16_t>(p.splits, rows, mgrid, a, st);
     else launch_merge<128, float>(p.splits, rows, mgrid, a, st);

@@ -205,6 +205,19 @@ def test_stream_short_pairs(d, B, L):
     check_attention(out, lse, ref_out, ref_lse, "bf16")
 
 
+def takes_stream(d, hq, hkv, B, L, batch, max_prefix):
+    """Whether the library streams this call by itself (bf16, row blocks of 256
+    rows): the stream's workspace is two partials per compute unit and the
+    tile offsets, whatever the batch."""
+    from paper_2606_02544_amd import binding
+    q = torch.empty((batch, B + L, hq, d), dtype=torch.bfloat16, device="meta")
+    k = torch.empty((batch, max(max_prefix, 1), hkv, d), dtype=torch.bfloat16, device="meta")
+    desc = binding.attention_desc(q, k, num_kv_heads=hkv, block_size=B, max_ref=L,
+                                  max_prefix_len=max_prefix)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    return binding.attention_workspace_size(desc) == cus * 2 * 256 * (d + 2) * 4 + 257 * 8
+
+
 @pytest.mark.parametrize("d,hq,B,L,batch,page,theta", [
     (128, 32, 32, 32, 34, 0, 0.0), (128, 32, 29, 24, 34, 16, 1e6), (64, 64, 32, 30, 18, 16, 0.0)],
     ids=["256rows", "212rows-paged-rope", "496rows-paged"])
@@ -218,6 +231,26 @@ def test_stream_whole_row_blocks(d, hq, B, L, batch, page, theta):
     out, lse = run_attention(DeviceInputs(inp), rope_theta=theta)
     ref_out, ref_lse = oracle.verify_attention(inp, rope_theta=theta)
     check_attention(out, lse, ref_out, ref_lse, "bf16")
+
+
+@pytest.mark.parametrize("d,hq,B", [(128, 32, 32), (64, 40, 20)], ids=["256rows", "200rows-d64"])
+def test_stream_row_blocks_precision(d, hq, B):
+    """Row blocks of more than 128 rows: pairs cut between two groups are as
+    exact as whole ones.  The same inputs with every pair in one chunk have one
+    rounding of each probability and one of the output, the cut pairs no other
+    (their partials are fp32), so the RMS errors agree but for which values get
+    rounded; a bf16 partial would add a rounding, 1.2 times the error."""
+    cfg = VerifyConfig(0, "blocks", "bf16", batch=17, num_q_heads=hq, num_kv_heads=8, head_dim=d,
+                       prefix=(900, 1100), block_size=B, max_ref=B, vocab=100, qkv_std=1.0)
+    assert takes_stream(d, hq, 8, B, B, 17, 1100)
+    inp = generate(cfg, seed=350 + B)
+    dev = DeviceInputs(inp)
+    ref_out, ref_lse = oracle.verify_attention(inp)
+    stream, whole = run_attention(dev), run_attention(dev, 1152)
+    for out, lse in (stream, whole):
+        check_attention(out, lse, ref_out, ref_lse, "bf16")
+    rms = [np.sqrt(np.mean((out - ref_out) ** 2)) for out, _ in (stream, whole)]
+    assert rms[0] <= 1.05 * rms[1], rms
 
 
 def test_stream_largest_batch():
