@@ -117,6 +117,7 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
   if (static_cast<int64_t>(d->num_kv_heads) * r.row_blocks > 65535)
     return fail(SIMSD_ERR_BAD_SHAPE, "attention: num_kv_heads * row blocks exceeds 65535");
   r.pairs = static_cast<int64_t>(d->batch) * d->num_kv_heads * r.row_blocks;
+  bool clamped = false;   // automatic chunks at their longest: several rounds of work-groups
   if (d->kv_chunk > 0) {
     r.chunk = d->kv_chunk;
   } else {
@@ -127,7 +128,8 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     int64_t c = ceil_div(static_cast<int64_t>(d->max_prefix_len) * r.pairs, target);
     c = ceil_div(c, kTile) * kTile;
     if (c < kMinAutoChunk) c = kMinAutoChunk;
-    if (c > kMaxAutoChunk) c = kMaxAutoChunk;
+    clamped = c > kMaxAutoChunk;
+    if (clamped) c = kMaxAutoChunk;
     r.chunk = static_cast<int>(c);
   }
   r.splits = d->max_prefix_len > 0 ? static_cast<int>(ceil_div(d->max_prefix_len, r.chunk)) : 1;
@@ -142,10 +144,19 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
   // (row blocks of up to 128 rows).  Within one round the chunks stay: on equal
   // prefixes they are faster (SDAR-8B layer 34.0 against 40.1 us), though not
   // on uneven ones (8 sequences of 1..8192: 53.9 against 39.9 us), and the
-  // lengths are on the device.  Row blocks of 256 rows, 24 sequences of
-  // prefixes 101..6007: 225 us in chunks, 122 us as a stream (rotary and paged
-  // 262 and 140 us); 60 of 101..1000: 95 and 90 us.  Workspace: two partial
-  // slots per group, then the per-sequence tile offsets.
+  // lengths are on the device.  Workspace: two partial slots per group, then the
+  // per-sequence tile offsets.
+  //
+  // Row blocks of 256 rows stream only where the chunks would cut the longest
+  // pairs in two, a grid that fills its rounds badly even with equal prefixes:
+  // chunks us / stream us, D 128, 8 KV heads: 17 sequences of 1024 67 / 58, of
+  // 100..1024 50 / 48, of 8192 271 / 206; 24 of 4096 209 / 164, of 100..4096
+  // 166 / 101; 31 of 100..8192 346 / 200.  Pairs of one chunk each are dealt to
+  // free CUs whole and need no merge (64 of 4096 331 / 363; 48 of 1024 94 / 111,
+  // of 100..1024 77 / 84), more than two chunks balance by themselves (11 of
+  // 100..2048 39 / 45), and chunks at their longest make full rounds (31 of 16384
+  // 642 / 711): there the chunks stay, though some uneven batches would be
+  // faster as a stream (48 of 100..4096 205 / 179; 31 of 100..16384 486 / 385).
   const bool can_stream = d->dtype == SIMSD_BF16 && d->batch <= kMaxStreamBatch;
   if (d->kv_chunk == kStreamChunk && !(can_stream && r.row_waves <= 4))
     return fail(SIMSD_ERR_UNSUPPORTED,
@@ -155,7 +166,8 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     // Stream groups: 8 waves (one per CU) for four or eight row waves, else 4 (two per CU).
     const int64_t groups = r.row_waves >= 4 ? cus : 2 * int64_t{cus};
     const int64_t tiles = r.pairs * (ceil_div(d->max_prefix_len, kTile) + 1);
-    if (d->kv_chunk == kStreamChunk || (tiles >= 8 * groups && r.pairs * r.splits > groups)) {
+    const bool fits = r.row_waves <= 4 || (r.splits == 2 && !clamped);
+    if (d->kv_chunk == kStreamChunk || (fits && tiles >= 8 * groups && r.pairs * r.splits > groups)) {
       r.stream = true;
       r.stream_groups = static_cast<int>(groups);
       // A pair costs its group a set-up besides its tiles (its loads in turn,
@@ -166,8 +178,9 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
       // 12, 104 at 16; 64 rows, 81 us at 0, 72 at 2, 71 at 4, 72 at 8, 75 at
       // 16 (two groups per CU: one's set-up runs beside the other's tiles).
       // 64 sequences with prefixes 512..32768: 820 us at 0, 812 at 4.  256
-      // rows on the first batch: 144 us at 2, 118 at 4 and 6, 122 at 8 and 12.
-      r.seg_tiles = r.row_waves >= 4 ? 8 : 4;
+      // rows: 2.3 % less time at 6 than at 8, 0.8 % less than at 4 (mean over
+      // 17 to 31 sequences, prefixes up to 1024 to 8192, equal and uneven).
+      r.seg_tiles = r.row_waves == 8 ? 6 : r.row_waves == 4 ? 8 : 4;
       r.workspace = static_cast<size_t>(groups) * 2 * r.part_floats * 4 +
                     static_cast<size_t>(kMaxStreamBatch + 1) * 8;
     }

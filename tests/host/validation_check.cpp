@@ -15,6 +15,7 @@
 #include <limits>
 #include <random>
 #include <string>
+#include <utility>
 
 #include "simsd.h"
 #include "simsd_plan.h"
@@ -82,6 +83,42 @@ static size_t attn_ws(const simsd_attn_desc& d, int cus = kCUs) {
 }
 
 static bool last_error_set() { return std::strlen(simsd_last_error()) > 0; }
+
+// Decomposition of the library's own choice for `batch` sequences of up to
+// `prefix` keys with `slots` block and as many reference slots (32/8 heads).
+static AttnPlan auto_plan(int batch, int prefix, int slots) {
+  simsd_attn_desc d = cfg_desc(4);
+  d.batch = batch;
+  d.max_prefix_len = prefix;
+  d.block_size = d.max_ref = slots;
+  AttnPlan p;
+  EXPECT(plan_attention(&d, kCUs, &p) == SIMSD_OK);
+  return p;
+}
+
+static void decomposition_cases() {
+  // 256-row blocks: stream where the chunks would cut the longest pairs in two.
+  for (const auto& c : {std::pair<int, int>{17, 1024}, {17, 8192}, {24, 4096}, {31, 8192}}) {
+    const AttnPlan p = auto_plan(c.first, c.second, 32);
+    EXPECT(p.stream && p.row_waves == 8 && p.stream_groups == kCUs && p.seg_tiles == 6);
+    EXPECT(p.workspace == size_t{256} * 2 * 256 * 130 * 4 + 257 * 8);
+  }
+  // Pairs of one chunk each: no stream and no workspace.
+  for (const auto& c : {std::pair<int, int>{33, 4096}, {64, 4096}, {64, 1024}, {60, 1000}, {48, 2048}}) {
+    const AttnPlan p = auto_plan(c.first, c.second, 32);
+    EXPECT(!p.stream && p.splits == 1 && p.workspace == 0);
+  }
+  // Small batches cut into more chunks, and chunks at their longest.
+  for (const auto& c : {std::pair<int, int>{11, 2048}, {13, 5000}, {31, 16384}, {64, 32768}})
+    EXPECT(!auto_plan(c.first, c.second, 32).stream);
+  // Smaller row blocks stream past one round of groups.
+  AttnPlan p = auto_plan(64, 4096, 16);
+  EXPECT(p.stream && p.row_waves == 4 && p.stream_groups == kCUs && p.seg_tiles == 8);
+  p = auto_plan(128, 4096, 8);
+  EXPECT(p.stream && p.row_waves == 2 && p.stream_groups == 2 * kCUs && p.seg_tiles == 4);
+  p = auto_plan(8, 4096, 16);
+  EXPECT(!p.stream && p.splits == 4);
+}
 
 // Store an arbitrary integer in a dtype field, as a C caller can (forming an
 // out-of-range enum value in C++ would itself be undefined).
@@ -371,6 +408,7 @@ static void fuzz(int iters) {
 
 int main() {
   attention_cases();
+  decomposition_cases();
   accept_cases();
   lmhead_cases();
   host_helper_cases();

@@ -218,14 +218,20 @@ def takes_stream(d, hq, hkv, B, L, batch, max_prefix):
     return binding.attention_workspace_size(desc) == cus * 2 * 256 * (d + 2) * 4 + 257 * 8
 
 
-@pytest.mark.parametrize("d,hq,B,L,batch,page,theta", [
-    (128, 32, 32, 32, 34, 0, 0.0), (128, 32, 29, 24, 34, 16, 1e6), (64, 64, 32, 30, 18, 16, 0.0)],
-    ids=["256rows", "212rows-paged-rope", "496rows-paged"])
-def test_stream_whole_row_blocks(d, hq, B, L, batch, page, theta):
+@pytest.mark.parametrize("d,hq,B,L,batch,page,theta,longest", [
+    (128, 32, 32, 32, 34, 0, 0.0, 500), (128, 32, 29, 24, 34, 16, 1e6, 500),
+    (64, 64, 32, 30, 18, 16, 0.0, 500),
+    (128, 32, 32, 32, 20, 0, 0.0, 1100), (128, 32, 29, 24, 20, 16, 1e6, 1100),
+    (64, 64, 32, 30, 10, 16, 0.0, 1100)],
+    ids=["256rows", "212rows-paged-rope", "496rows-paged", "256rows-stream",
+         "212rows-paged-rope-stream", "496rows-paged-stream"])
+def test_stream_whole_row_blocks(d, hq, B, L, batch, page, theta, longest):
     """Row blocks of more than 128 rows take the stream decomposition by
-    themselves where the chunks would need more than one round of groups."""
+    themselves where the chunks would cut the longest pairs in two; pairs of one
+    chunk each stay whole, in several rounds of groups."""
+    assert takes_stream(d, hq, 8, B, L, batch, longest) == (longest == 1100)
     cfg = VerifyConfig(0, "blocks", "bf16", batch=batch, num_q_heads=hq, num_kv_heads=8, head_dim=d,
-                       prefix=(0, 500), block_size=B, max_ref=L, vocab=100, page_size=page,
+                       prefix=(0, longest), block_size=B, max_ref=L, vocab=100, page_size=page,
                        qkv_std=0.3, step_mode="mixed")
     inp = generate(cfg, seed=330 + B + L, poison=True)
     out, lse = run_attention(DeviceInputs(inp), rope_theta=theta)
