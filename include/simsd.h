@@ -54,7 +54,10 @@
  *    *_workspace_size() call returns (it may be 0, and then the pointer may
  *    be NULL).  It holds per-chunk partial results between the kernels of one
  *    call; its contents need no initialisation and are meaningless afterwards.
- *    Two calls in flight at the same time need two workspaces.
+ *    Two calls in flight at the same time need two workspaces.  A
+ *    call with less returns SIMSD_ERR_WORKSPACE, except that
+ *    simsd_verify_attention takes a slower decomposition if one fits it (fp32,
+ *    or more than 128 packed rows: Hq / Hkv * (B + L)).
  *  - Grid sizes follow the compute-unit count of the device a call's stream
  *    belongs to (queried once per device through the HIP device attributes
  *    and cached; a compute-partitioned MI355X reports its partition's units).

@@ -328,9 +328,14 @@ def _attention_hkv(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens, 
 
 
 @functools.lru_cache(maxsize=1024)
-def _attn_desc(*fields) -> AttnDesc:
-    """AttnDesc of these field values (read only: calls share it)."""
-    return AttnDesc(*fields)
+def _attn_desc(device: torch.device, *fields):
+    """AttnDesc of these field values (read only: calls share it) and the
+    workspace bytes of its call on `device`."""
+    desc = AttnDesc(*fields)
+    if device.type != "cuda":
+        return desc, attention_workspace_size(desc)
+    with torch.cuda.device(device):
+        return desc, attention_workspace_size(desc)
 
 
 @functools.lru_cache(maxsize=1024)
@@ -346,16 +351,19 @@ def _lmhead_desc(*fields) -> LmheadDesc:
 _NEEDS_WORKSPACE = 5             # SIMSD_ERR_WORKSPACE
 
 
-def _run(fn, head, args, workspace, device, handle, kind, size_of, desc):
+def _run(fn, head, args, workspace, device, handle, kind, size_of, desc, nbytes=0):
     """fn(*head, *args, workspace, bytes, stream).  Without a caller's workspace
-    the buffer held for this stream is offered as it is; the library refuses one
-    that is too small before it enqueues anything, and only then is the size
+    the buffer held for this stream is offered, grown to `nbytes` first (the
+    attention takes a slower decomposition in a smaller one); the library refuses
+    one that is too small before it enqueues anything, and only then is the size
     asked for and the buffer grown."""
     if workspace is not None:
         _tensor("workspace", workspace, (None,), None, device)
         _check(fn(*head, *args, workspace.data_ptr(), _nbytes(workspace), handle))
         return
     buf = WORKSPACES.held(device, handle, kind)
+    if buf is None or buf.numel() < nbytes:
+        buf = WORKSPACES.get(device, handle, kind, nbytes)
     status = fn(*head, *args, *((None, 0) if buf is None else (buf.data_ptr(), buf.numel())), handle)
     if status == _NEEDS_WORKSPACE:
         buf = WORKSPACES.get(device, handle, kind, size_of(desc))
@@ -387,8 +395,11 @@ def verify_attention(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens
     if desc is None:
         st = (k_cache if max_prefix_len > 0 else k_new).stride()
         pages = block_table.shape[1] if block_table is not None and page_size > 0 else 0
-        desc = _attn_desc(b, hq, hkv, d, block_size, max_ref, max_prefix_len, page_size, pages,
-                          kv_chunk, st[0], st[1], st[2], scale, _dtype_code(q.dtype), rope_theta)
+        desc, nbytes = _attn_desc(dev, b, hq, hkv, d, block_size, max_ref, max_prefix_len,
+                                  page_size, pages, kv_chunk, st[0], st[1], st[2], scale,
+                                  _dtype_code(q.dtype), rope_theta)
+    else:
+        nbytes = 0 if workspace is not None else attention_workspace_size(desc)
     if out is None:
         out = torch.empty_like(q, memory_format=torch.contiguous_format)
     if lse is None and want_lse:
@@ -397,7 +408,8 @@ def verify_attention(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens
          (q.data_ptr(), k_new.data_ptr(), v_new.data_ptr(), _addr(k_cache), _addr(v_cache),
           _addr(block_table), prefix_lens.data_ptr(), step_map.data_ptr(), num_ref.data_ptr(),
           out.data_ptr(), _addr(lse)),
-         workspace, dev, _stream_of(stream, dev).cuda_stream, "attn", attention_workspace_size, desc)
+         workspace, dev, _stream_of(stream, dev).cuda_stream, "attn", attention_workspace_size, desc,
+         nbytes)
     return out, lse
 
 

@@ -95,7 +95,7 @@ extern "C" simsd_status simsd_verify_attention(
     int cus = 0;
     const hipError_t qe = stream_cus(stream, &cus);
     AttnPlan p;
-    simsd_status st = plan_attention(desc, cus, &p);
+    simsd_status st = plan_attention_within(desc, cus, workspace, workspace_bytes, &p);
     if (st != SIMSD_OK) return st;
     st = check_attention_args(desc, p, q, k_new, v_new, k_cache, v_cache, block_table,
                               prefix_lens, step_map, num_ref, out, lse, workspace,

@@ -39,7 +39,7 @@ static bool known_dtype(const simsd_dtype& field) {
   return v == SIMSD_F32 || v == SIMSD_BF16;
 }
 
-simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
+simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p, bool spare) {
   if (!d || !p) return fail(SIMSD_ERR_NULL_POINTER, "attention: descriptor is NULL");
   if (cus < 1) return fail(SIMSD_ERR_HIP, "attention: the device reports no compute units");
   if (!known_dtype(d->dtype))
@@ -111,7 +111,7 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     r.row_waves = 4;
     const int64_t pieces = static_cast<int64_t>(d->batch) * d->num_kv_heads * ceil_div(r.rows, 32) *
                            std::max<int64_t>(1, ceil_div(d->max_prefix_len, kTile));
-    r.rows_pb = r.rows <= 16 || pieces < 6 * int64_t{cus} ? 16 : 32;
+    r.rows_pb = !spare && (r.rows <= 16 || pieces < 6 * int64_t{cus}) ? 16 : 32;
   }
   r.row_blocks = static_cast<int>(ceil_div(r.rows, r.rows_pb));
   if (static_cast<int64_t>(d->num_kv_heads) * r.row_blocks > 65535)
@@ -123,8 +123,9 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
   } else {
     // Split the longest prefix so that about as many work-groups exist as the
     // chip holds at once: one group per CU, two for the two-row-wave groups
-    // and the fp32 ones.
-    const int64_t target = d->dtype == SIMSD_BF16 && r.row_waves >= 4 ? cus : 2 * int64_t{cus};
+    // and the fp32 ones (one if scratch is to be spared).
+    const bool one = r.row_waves >= 4 && (d->dtype == SIMSD_BF16 || spare);
+    const int64_t target = one ? cus : 2 * int64_t{cus};
     int64_t c = ceil_div(static_cast<int64_t>(d->max_prefix_len) * r.pairs, target);
     c = ceil_div(c, kTile) * kTile;
     if (c < kMinAutoChunk) c = kMinAutoChunk;
@@ -166,7 +167,7 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
     // Stream groups: 8 waves (one per CU) for four or eight row waves, else 4 (two per CU).
     const int64_t groups = r.row_waves >= 4 ? cus : 2 * int64_t{cus};
     const int64_t tiles = r.pairs * (ceil_div(d->max_prefix_len, kTile) + 1);
-    const bool fits = r.row_waves <= 4 || (r.splits == 2 && !clamped);
+    const bool fits = r.row_waves <= 4 || (r.splits == 2 && !clamped && !spare);
     if (d->kv_chunk == kStreamChunk || (fits && tiles >= 8 * groups && r.pairs * r.splits > groups)) {
       r.stream = true;
       r.stream_groups = static_cast<int>(groups);
@@ -190,6 +191,18 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p) {
   // theta^(-2i/d) = exp2(i * rope_step), rope_step = -2 log2(theta) / d
   r.rope_step = d->rope_theta > 0.f ? -2.0f * std::log2(d->rope_theta) / d->head_dim : 0.f;
   *p = r;
+  return SIMSD_OK;
+}
+
+simsd_status plan_attention_within(const simsd_attn_desc* d, int cus, const void* workspace,
+                                   size_t workspace_bytes, AttnPlan* p) {
+  auto fits = [&](const AttnPlan& r) {
+    return r.workspace == 0 || (workspace && aligned16(workspace) && workspace_bytes >= r.workspace);
+  };
+  const simsd_status st = plan_attention(d, cus, p);
+  if (st != SIMSD_OK || fits(*p)) return st;
+  AttnPlan s;
+  if (plan_attention(d, cus, &s, true) == SIMSD_OK && fits(s)) *p = s;
   return SIMSD_OK;
 }
 

@@ -89,7 +89,12 @@ void set_error(const std::string& msg);
 
 // `cus`: compute units of the device the call runs on (it sizes the grids and
 // the stream decomposition's workspace); must be >= 1.
-simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p);
+// `spare`: the decomposition that needs less scratch (fp32: 32-row blocks, one
+// group per CU; 256-row blocks: chunks), for a caller with less than the size asked.
+simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p, bool spare = false);
+// The plan for a call with this workspace: the spare one if only that fits.
+simsd_status plan_attention_within(const simsd_attn_desc* d, int cus, const void* workspace,
+                                   size_t workspace_bytes, AttnPlan* p);
 simsd_status check_attention_args(const simsd_attn_desc* d, const AttnPlan& p, const void* q,
                                   const void* k_new, const void* v_new, const void* k_cache,
                                   const void* v_cache, const int32_t* block_table,

@@ -120,6 +120,42 @@ static void decomposition_cases() {
   EXPECT(!p.stream && p.splits == 4);
 }
 
+// A workspace for the decomposition that needs less is accepted, and nothing smaller.
+static void spare_cases() {
+  simsd_attn_desc wide = cfg_desc(4);                    // 256-row blocks, streamed
+  wide.batch = 17;
+  wide.max_prefix_len = 1024;
+  simsd_attn_desc f32 = cfg_desc(3), f32_whole = cfg_desc(3);
+  f32.dtype = f32_whole.dtype = SIMSD_F32;
+  f32.batch = 2;
+  struct Case { simsd_attn_desc d; size_t less; };
+  // less: two chunks of 17 x 8 pairs; four of 2 x 8 x 4 pairs; whole pairs.
+  const Case cases[] = {{wide, size_t{136} * 2 * 256 * 130 * 4},
+                        {f32, size_t{64} * 4 * 32 * 130 * 4},
+                        {f32_whole, 0}};
+  for (const Case& c : cases) {
+    AttnPlan p, spare, q;
+    EXPECT(plan_attention(&c.d, kCUs, &p) == SIMSD_OK);
+    EXPECT(plan_attention(&c.d, kCUs, &spare, true) == SIMSD_OK);
+    EXPECT(spare.workspace == c.less && spare.workspace < p.workspace && !spare.stream);
+    EXPECT(plan_attention_within(&c.d, kCUs, FAKE, p.workspace, &q) == SIMSD_OK);
+    EXPECT(q.workspace == p.workspace && q.splits == p.splits && q.stream == p.stream);
+    EXPECT(plan_attention_within(&c.d, kCUs, FAKE, p.workspace - 1, &q) == SIMSD_OK);
+    EXPECT(q.workspace == c.less && q.splits == spare.splits && !q.stream);
+    EXPECT(plan_attention_within(&c.d, kCUs, c.less ? FAKE : nullptr, c.less, &q) == SIMSD_OK);
+    EXPECT(q.workspace == c.less);
+    if (c.less) {
+      EXPECT(plan_attention_within(&c.d, kCUs, FAKE, c.less - 1, &q) == SIMSD_OK);
+      EXPECT(q.workspace == p.workspace);                // what the refusal asks for
+    }
+  }
+  simsd_attn_desc x = cfg_desc(5);                       // no spare form: 64-row stream
+  AttnPlan p, q;
+  EXPECT(plan_attention(&x, kCUs, &p) == SIMSD_OK && p.stream);
+  EXPECT(plan_attention_within(&x, kCUs, FAKE, p.workspace - 1, &q) == SIMSD_OK);
+  EXPECT(q.stream && q.workspace == p.workspace);
+}
+
 // Store an arbitrary integer in a dtype field, as a C caller can (forming an
 // out-of-range enum value in C++ would itself be undefined).
 static void set_dtype(simsd_dtype& field, int v) { std::memcpy(&field, &v, sizeof v); }
@@ -409,6 +445,7 @@ static void fuzz(int iters) {
 int main() {
   attention_cases();
   decomposition_cases();
+  spare_cases();
   accept_cases();
   lmhead_cases();
   host_helper_cases();

@@ -259,6 +259,42 @@ def test_stream_row_blocks_precision(d, hq, B):
     assert rms[0] <= 1.05 * rms[1], rms
 
 
+@pytest.mark.parametrize("dt,batch,prefix,spare", [
+    ("bf16", 17, (300, 1024), 136 * 2 * 256 * 130 * 4), ("f32", 2, (1700, 2000), 64 * 4 * 32 * 130 * 4),
+    ("f32", 8, (400, 700), 16)], ids=["256rows", "f32", "f32-whole"])
+def test_spare_workspace(dt, batch, prefix, spare):
+    """With a workspace smaller than the size asked for but enough for the
+    decomposition that needs less, the call takes that one and stays inside it;
+    without a workspace of the caller's it has the whole size."""
+    from paper_2606_02544_amd import binding
+    slots = 32 if dt == "bf16" else 16
+    cfg = VerifyConfig(0, "spare", dt, batch=batch, num_q_heads=32, num_kv_heads=8, head_dim=128,
+                       prefix=prefix, block_size=slots, max_ref=slots, vocab=100, qkv_std=0.3,
+                       step_mode="mixed")
+    inp = generate(cfg, seed=360 + batch, poison=True)
+    d = DeviceInputs(inp)
+    ref_out, ref_lse = oracle.verify_attention(inp)
+    desc = binding.attention_desc(d.q, d.k_cache, num_kv_heads=8, block_size=slots, max_ref=slots,
+                                  max_prefix_len=cfg.max_prefix)
+    need = binding.attention_workspace_size(desc)
+    assert need > spare
+    store = torch.full((need + 256,), 0x55, dtype=torch.uint8, device="cuda")
+    for own, size in ((True, spare), (True, need), (False, need)):
+        store.fill_(0x55)
+        binding.WORKSPACES.clear()
+        out, lse = binding.verify_attention(
+            d.q, d.k_new, d.v_new, d.k_cache, d.v_cache, None, d.prefix_lens, d.step_map, d.num_ref,
+            block_size=slots, max_ref=slots, max_prefix_len=cfg.max_prefix,
+            workspace=store[:size] if own else None)
+        torch.cuda.synchronize()
+        assert torch.all(store[size if own else 0:] == 0x55)
+        if not own:
+            assert binding.WORKSPACES.held(d.q.device, torch.cuda.current_stream().cuda_stream,
+                                           "attn").numel() == need
+        check_attention(out.float().cpu().double().numpy(), lse.cpu().double().numpy(), ref_out,
+                        ref_lse, dt)
+
+
 def test_stream_largest_batch():
     """The stream decomposition at its largest batch (256 sequences): the
     per-sequence tile offsets are scanned over all 256 entries; ragged
