@@ -10,6 +10,7 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import operator
 import os
 from typing import Optional
 
@@ -327,6 +328,9 @@ def _attention_hkv(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens, 
         return None
 
 
+# The cached descriptors are keyed by plain numbers: a tensor or array given for
+# one is read on every call (its content may have changed, and it hashes by
+# identity or not at all), and a float is no key for an integer field.
 @functools.lru_cache(maxsize=1024)
 def _attn_desc(device: torch.device, *fields):
     """AttnDesc of these field values (read only: calls share it) and the
@@ -395,6 +399,11 @@ def verify_attention(q, k_new, v_new, k_cache, v_cache, block_table, prefix_lens
     if desc is None:
         st = (k_cache if max_prefix_len > 0 else k_new).stride()
         pages = block_table.shape[1] if block_table is not None and page_size > 0 else 0
+        if not (type(block_size) is type(max_ref) is type(max_prefix_len) is type(page_size)
+                is type(kv_chunk) is int and type(scale) is type(rope_theta) is float):
+            block_size, max_ref, max_prefix_len, page_size, kv_chunk = map(
+                operator.index, (block_size, max_ref, max_prefix_len, page_size, kv_chunk))
+            scale, rope_theta = ctypes.c_float(scale).value, ctypes.c_float(rope_theta).value
         desc, nbytes = _attn_desc(dev, b, hq, hkv, d, block_size, max_ref, max_prefix_len,
                                   page_size, pages, kv_chunk, st[0], st[1], st[2], scale,
                                   _dtype_code(q.dtype), rope_theta)
@@ -467,7 +476,7 @@ def verify_accept(logits, draft_ids, step_map, num_ref, *, chunks_per_row: int =
     draft_prob = _given("draft_prob", draft_prob, (b, L), torch.float32, dev)
     accept_len = _given("accept_len", accept_len, (b,), torch.int32, dev)
     if desc is None:
-        desc = _accept_desc(b, B, L, V, chunks_per_row, _dtype_code(logits.dtype))
+        desc = _accept_desc(b, B, L, V, operator.index(chunks_per_row), _dtype_code(logits.dtype))
     _run(lib().simsd_verify_accept, (ctypes.byref(desc),),
          (logits.data_ptr(), draft_ids.data_ptr(), step_map.data_ptr(), num_ref.data_ptr(),
           target_ids.data_ptr(), confidence.data_ptr(), draft_prob.data_ptr(),
@@ -517,8 +526,8 @@ def verify_accept_sampled(logits, draft_logits, draft_ids, step_map, num_ref, un
     accept_len = _given("accept_len", accept_len, (b,), torch.int32, dev)
     correction = _given("correction", correction, (b,), torch.int32, dev)
     if desc is None:
-        desc = _accept_desc(b, B, L, V, chunks_per_row, _dtype_code(logits.dtype))
-    _run(lib().simsd_verify_accept_sampled, (ctypes.byref(desc), temperature),
+        desc = _accept_desc(b, B, L, V, operator.index(chunks_per_row), _dtype_code(logits.dtype))
+    _run(lib().simsd_verify_accept_sampled, (ctypes.byref(desc), ctypes.c_float(temperature)),
          (logits.data_ptr(), draft_logits.data_ptr(), draft_ids.data_ptr(), step_map.data_ptr(),
           num_ref.data_ptr(), uniforms.data_ptr(), p_target.data_ptr(), p_draft.data_ptr(),
           accept_len.data_ptr(), correction.data_ptr()),

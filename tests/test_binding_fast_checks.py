@@ -2,7 +2,9 @@
 (CPU tensors: nothing is launched)."""
 
 import itertools
+import types
 
+import numpy as np
 import pytest
 import torch
 
@@ -96,3 +98,73 @@ def test_accept_and_lmhead(kind):
     for name, t in itertools.chain.from_iterable(((n, t) for t in spoiled(x)) for n, x in a.items()):
         c = dict(a, **{name: t})
         assert outcome(short, c) == outcome(full, c), name
+
+
+@pytest.fixture
+def calls(monkeypatch):
+    """The descriptors that calls hand to the library, as (field, value) dicts."""
+    seen = []
+
+    def record(desc, *_):
+        seen.append({n: getattr(desc._obj, n) for n, _ in desc._obj._fields_})
+        return 0
+
+    monkeypatch.setattr(binding, "lib", lambda: types.SimpleNamespace(
+        simsd_verify_attention=record, simsd_verify_accept=record, simsd_verify_accept_sampled=record,
+        simsd_verify_attention_workspace_size=lambda desc: 0))
+    return seen
+
+
+STREAM = types.SimpleNamespace(cuda_stream=0)
+
+
+@pytest.mark.parametrize("name", ["scale", "rope_theta"])
+def test_float_arguments_are_read_on_every_call(calls, name):
+    a, kw = attention_args()
+    del a["out"], a["lse"]
+    for box in (torch.tensor(0.5), np.array(0.5)):
+        for value in (0.5, 0.25, 2.0):
+            box[...] = value
+            binding.verify_attention(*a.values(), **kw, **{name: box}, stream=STREAM)
+            assert calls[-1][name] == value
+    for other in (1, np.float32(0.75), 0.3):
+        binding.verify_attention(*a.values(), **kw, **{name: other}, stream=STREAM)
+        assert calls[-1][name] == np.float32(other)
+    for bad in ("0.5", None):
+        with pytest.raises(TypeError):
+            binding.verify_attention(*a.values(), **kw, **{name: bad}, stream=STREAM)
+
+
+def test_integer_arguments_are_read_on_every_call(calls):
+    a, kw = attention_args()
+    del a["out"], a["lse"]
+    for box in (torch.tensor(64), np.array(64)):
+        for value in (64, 128, 0):
+            box[...] = value
+            binding.verify_attention(*a.values(), **kw, kv_chunk=box, stream=STREAM)
+            assert calls[-1]["kv_chunk"] == value
+    for name, value in dict(kw, kv_chunk=64).items():          # a float is refused, also once seen as an int
+        with pytest.raises(TypeError):
+            binding.verify_attention(*a.values(), **dict(kw, kv_chunk=64, **{name: float(value)}), stream=STREAM)
+
+
+def test_chunks_per_row_is_read_on_every_call(calls):
+    b, B, L, V = 2, 4, 3, 10
+    logits, side = torch.zeros(b, B, V), torch.zeros(b, L, V)
+    ints = (torch.zeros(b, L, dtype=torch.int32), torch.zeros(b, B, dtype=torch.int32),
+            torch.zeros(b, dtype=torch.int32))
+
+    def greedy(n):
+        binding.verify_accept(logits, *ints, chunks_per_row=n, stream=STREAM)
+
+    def sampled(n):
+        binding.verify_accept_sampled(logits, side, *ints, torch.zeros(b, L + 1), chunks_per_row=n, stream=STREAM)
+
+    for call in (greedy, sampled):
+        box = torch.tensor(2)
+        for value in (2, 5, 0):
+            box.fill_(value)
+            call(box)
+            assert calls[-1]["chunks_per_row"] == value
+        with pytest.raises(TypeError):
+            call(2.0)
