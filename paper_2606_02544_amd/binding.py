@@ -366,7 +366,7 @@ def _run(fn, head, args, workspace, device, handle, kind, size_of, desc, nbytes=
         _check(fn(*head, *args, workspace.data_ptr(), _nbytes(workspace), handle))
         return
     buf = WORKSPACES.held(device, handle, kind)
-    if buf is None or buf.numel() < nbytes:
+    if nbytes and (buf is None or buf.numel() < nbytes):
         buf = WORKSPACES.get(device, handle, kind, nbytes)
     status = fn(*head, *args, *((None, 0) if buf is None else (buf.data_ptr(), buf.numel())), handle)
     if status == _NEEDS_WORKSPACE:
