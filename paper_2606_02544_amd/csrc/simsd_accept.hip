@@ -103,10 +103,12 @@ __device__ inline void load_vec(const void* row, int64_t v, float (&x)[VEC]) {
 // Scan vectors [v0, v1) of a row (`row` is vector 0, 16-byte aligned, and holds
 // vocabulary entry `first`), and entry `extra` of the row at `row0` if it is not
 // negative (the entries outside the aligned vectors); returns this
-// work-group's (max, index, sum).
+// work-group's (max, index, sum).  (Inlined by force: as a call it costs the
+// bf16 scan 68 VGPRs for 39, sampled accept of 16 x 32 rows 73.6 -> 74.4 us.)
 template <bool BF16, int VEC>
-__device__ Best scan_chunk(const void* row, int64_t v0, int64_t v1, int first, const void* row0,
-                           int extra, int tid, float cl, Best* s_red) {
+__device__ __attribute__((always_inline)) inline Best scan_chunk(
+    const void* row, int64_t v0, int64_t v1, int first, const void* row0, int extra, int tid, float cl,
+    Best* s_red) {
   float mx = kNegInf, sm = 0.f;
   int64_t vbest = -1;
   constexpr int U = 4;
@@ -158,8 +160,11 @@ __device__ Best scan_chunk(const void* row, int64_t v0, int64_t v1, int first, c
     me.sm = sm;
   }
   if (extra >= 0) {
+    // As in the vectors, NaN is no maximum and makes the sum NaN: it takes the
+    // lowest finite value's place (combine drops a side whose maximum is -inf).
     const float x = load_elem<BF16>(row0, extra);
-    if (x > kNegInf) me = combine(me, Best{x, extra, 1.f}, cl);
+    if (x != kNegInf)
+      me = combine(me, Best{fmaxf(x, -__FLT_MAX__), x > kNegInf ? extra : kNoIndex, x - x + 1.f}, cl);
   }
   me = wave_reduce(me, cl);
   const int lane = tid & 63, wave = tid >> 6;

@@ -49,3 +49,31 @@ def test_unaligned_rows(dtype, V):
         torch.cuda.synchronize()
         check_accept(tuple(t.cpu().double().numpy() if t.dtype == torch.float32 else t.cpu().numpy()
                            for t in got), ref)
+
+
+@pytest.mark.parametrize("bad", [np.nan, np.inf])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [2, 9, 2055, 20007, 20008])
+def test_nan_and_inf_at_row_ends(dtype, V, bad):
+    """A NaN or +inf as a row's first or last entry, on rows of every alignment:
+    the probabilities are NaN wherever the entry falls; NaN is never the target
+    and +inf is."""
+    from paper_2606_02544_amd import binding
+    rng = np.random.default_rng(V)
+    b, B = 2, 8
+    x = (rng.standard_normal((b, B, V)) * 2).clip(-12, 12).astype(np.float32)
+    x[0, :, 0] = bad
+    x[1, :, V - 1] = bad
+    stored = bf16_bits_from_f32(x) if dtype == "bf16" else x
+    if np.isnan(bad) and dtype == "bf16":
+        stored[np.isnan(x)] = 0x7fc0
+    wide = np.where(np.isnan(x), -np.inf, x if dtype == "f32" else (stored.astype(np.uint32) << 16).view(np.float32))
+    step = np.tile(np.arange(1, B + 1, dtype=np.int32), (b, 1))
+    target = wide.argmax(-1).astype(np.int32)
+    for cpr in (0, 2):
+        t, c, p, a = binding.verify_accept(dev_tensor(stored, dtype), int_tensor(target), int_tensor(step),
+                                           int_tensor(np.full(b, B)), chunks_per_row=cpr)
+        torch.cuda.synchronize()
+        np.testing.assert_array_equal(t.cpu().numpy(), target)
+        assert torch.all(a == B)
+        assert torch.all(torch.isnan(c)) and torch.all(torch.isnan(p)), (cpr, c, p)
