@@ -907,7 +907,7 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
   const int items = np + (my_new ? 1 : 0);
   // Address of key `key` of an item, `base` and the rest uniform: keys past the
   // item's last one read that one (their scores are masked and their values
-  // finite).  Prefix and new slots differ in the uniform values only.
+  // cleared).  Prefix and new slots differ in the uniform values only.
   auto key_at = [&](const float* base, bool is_new, int key, int page) __attribute__((always_inline)) {
     const int64_t st = is_new ? newrow : a.cs_tok;
     key = min(key, is_new ? a.n_new - 1 : w.kend - 1);
@@ -1090,6 +1090,15 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
         s[r][j] = __builtin_amdgcn_exp2f(fmaf(s[r][j], sl2, -moff));
         l_run[r] += s[r][j];
       }
+    }
+    // Keys past the item's last one hold that one's values, which may be infinite.
+    const int left = (is_new ? a.n_new : w.kend) - k0;
+    if (left < SUB) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+        if (4 * q + j >= left)
+#pragma unroll
+          for (int u = 0; u < VU; ++u) vx[j][u] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int j = 0; j < 4; ++j)

@@ -4,6 +4,7 @@ slots as one more sub-tile per wave.  Same tolerance as the other fp32 tests
 (1e-5 absolute: outputs are averages of N(0, 1) values, so a sum over n keys is
 off by a few ulps of 1, about sqrt(n) * 6e-8 < 2e-6 at n = 1100)."""
 
+import numpy as np
 import pytest
 
 import oracle
@@ -44,3 +45,23 @@ def test_f32_tiles(case):
     out, lse = run_attention(DeviceInputs(inp), kv_chunk, rope_theta=theta)
     ref_out, ref_lse = oracle.verify_attention(inp, rope_theta=theta)
     check_attention(out, lse, ref_out, ref_lse, "f32")
+
+
+@pytest.mark.parametrize("prefix,B,L", [(37, 5, 3), (16, 9, 8), (1, 1, 0)])
+def test_f32_infinite_last_value(prefix, B, L):
+    """An infinity among the values of the prefix's or the block's last key
+    reaches the rows that see the key as an infinity, also where the key's 16-key
+    sub-tile has no other keys to fill it; the other dims are untouched."""
+    cfg = VerifyConfig(0, "f32", "f32", batch=2, num_q_heads=4, num_kv_heads=2, head_dim=64,
+                       prefix=(prefix, prefix), block_size=B, max_ref=L, vocab=100, qkv_std=0.5)
+    inp = generate(cfg, seed=540 + prefix)
+    clean = run_attention(DeviceInputs(inp), 64)[0]
+    inp.v_cache[:, prefix - 1, :, 3] = np.inf
+    inp.v_cache[:, prefix - 1, :, 40] = -np.inf
+    # The last slot is a verification row, or a block slot where nothing is drafted.
+    inp.v_new[:, -1, :, 7] = np.inf
+    out = run_attention(DeviceInputs(inp), 64)[0]
+    assert np.all(out[..., 3] == np.inf) and np.all(out[..., 40] == -np.inf)
+    assert np.all(out[:, -1, :, 7] == np.inf)
+    rest = np.delete(np.arange(64), (3, 7, 40))
+    np.testing.assert_array_equal(out[..., rest], clean[..., rest])
