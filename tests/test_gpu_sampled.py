@@ -11,6 +11,8 @@ run, and a draw within 1e-4 * Z of a CDF boundary is checked for validity
 within 1e-4 relative.
 """
 
+import types
+
 import numpy as np
 import pytest
 import torch
@@ -18,7 +20,7 @@ import torch
 import oracle
 from oracle import sampled as osmp
 from oracle.widen import widen
-from synth import VerifyConfig, config_by_id, generate, generate_draft_side
+from synth import VerifyConfig, bf16_bits_from_f32, config_by_id, generate, generate_draft_side
 from gpu_util import dev_tensor, int_tensor
 
 pytestmark = pytest.mark.gpu
@@ -97,7 +99,7 @@ SAMPLED_CASES = [
     ("cfg1", 0.7, 3, 2),
     ("mixed_bf16", 1.0, 0, 3),
     ("mixed_bf16", 0.8, 5, 4),
-    ("mixed_bf16_v1021", 1.0, 2, 5),      # V not a multiple of 8: scalar path
+    ("mixed_bf16_v1021", 1.0, 2, 5),      # V not a multiple of 8: one-entry draw loads
     ("mixed_f32", 1.3, 0, 6),
 ]
 
@@ -159,4 +161,71 @@ def test_sampled_large_vocab_bf16():
     dlog, u = generate_draft_side(inp)
     u = nudge(inp, dlog, u, 1.0)
     got = run_sampled(inp, dlog, u, 1.0)
+    check_sampled(inp, dlog, u, 1.0, got)
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("V", [1, 2, 7, 9, 17, 4099])
+def test_sampled_small_and_odd_vocab(dtype, V):
+    """Rows that start at every alignment, shorter than a vector up to a few
+    hundred of them, on the target's and on the drafter's side."""
+    cfg = VerifyConfig(0, "vocab", dtype, batch=9, num_q_heads=1, num_kv_heads=1, head_dim=64,
+                       prefix=(0, 8), block_size=16, max_ref=12, vocab=V, plant=0.6, step_mode="mixed")
+    inp = generate(cfg, seed=20 + V, bad_draft_rate=0.2)
+    dlog, u = generate_draft_side(inp)
+    u = nudge(inp, dlog, u, 0.9)
+    for cpr in (0, 3):
+        check_sampled(inp, dlog, u, 0.9, run_sampled(inp, dlog, u, 0.9, cpr))
+
+
+KEPT = 4             # loads of a thread's run that the draw keeps in registers
+
+
+def draw_runs(V, dtype, batch):
+    """(entries per load, loads per draw chunk, loads per thread's run) of the draw."""
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    width = 8 if dtype == "bf16" else 4
+    vec = width if V % width == 0 else 1
+    nvec = -(-V // vec)
+    chunks = max(1, min(-(-2 * cus // batch), max(1, nvec // 256), 256))
+    per_chunk = -(-nvec // chunks)
+    return vec, per_chunk, -(-per_chunk // 256)
+
+
+@pytest.mark.parametrize("dtype,V,batch", [("f32", 50001, 16), ("bf16", 151935, 16), ("bf16", 151936, 32),
+                                           ("f32", 151936, 16)])
+def test_draw_in_long_runs(dtype, V, batch):
+    """Draws that end in every part of a thread's run of loads: among those kept
+    in registers, among those read again, at the run's first and last entry.  A
+    planted entry holds about half of the residual and the draw aims at its
+    middle, so the token is exact."""
+    vec, per_chunk, run = draw_runs(V, dtype, batch)
+    assert run > KEPT
+    rng = np.random.default_rng(V + batch)
+    logits = (rng.standard_normal((batch, 1, V), dtype=np.float32) * 2).clip(-12, 12)
+    dlog = (rng.standard_normal((batch, 1, V), dtype=np.float32) * 2).clip(-12, 12)
+    offs = [0, KEPT - 1, KEPT, run - 1]
+    want = np.zeros(batch, np.int32)
+    for s in range(batch):
+        chunk, thread = int(rng.integers(0, -(-V // vec) // per_chunk)), int(rng.integers(0, per_chunk // run))
+        entry = 0 if s // len(offs) % 2 else vec - 1
+        want[s] = (chunk * per_chunk + thread * run + offs[s % len(offs)]) * vec + entry
+    assert want.max() < V
+    at = np.arange(batch)
+    logits[at, 0, want] = 13.0
+    dlog[at, 0, want] = -12.0
+    if dtype == "bf16":
+        logits, dlog = bf16_bits_from_f32(logits), bf16_bits_from_f32(dlog)
+    u = np.full((batch, 2), 0.5, np.float32)
+    for s in range(batch):
+        q, _ = osmp.residual_row(logits[s, 0], dlog[s, 0], 1.0, dtype)
+        cdf = np.cumsum(q)
+        assert q[want[s]] > 0.2 * cdf[-1]
+        u[s, 1] = (cdf[want[s]] - q[want[s]] / 2) / cdf[-1]
+    cfg = VerifyConfig(0, "runs", dtype, batch=batch, num_q_heads=1, num_kv_heads=1, head_dim=64,
+                       prefix=0, block_size=1, max_ref=1, vocab=V)
+    inp = types.SimpleNamespace(cfg=cfg, logits=logits, draft_ids=np.full((batch, 1), V, np.int32),
+                                step_map=np.ones((batch, 1), np.int32), num_ref=np.ones(batch, np.int32))
+    got = run_sampled(inp, dlog, u, 1.0)
+    np.testing.assert_array_equal(got[3], want)
     check_sampled(inp, dlog, u, 1.0, got)
