@@ -2,8 +2,8 @@
 remarks (hipcc for gfx950 on the CPU, no GPU needed).  A spill inside a tile
 loop is costly here: the reload waits on vector memory, which completes in
 issue order, so it also waits for every tile load in flight.  Every kernel
-must compile without VGPR spills, except the rotary variants of the stream
-decomposition, which spill a few values outside their tile loops."""
+must compile without VGPR spills (the stream decomposition's rotary variants
+spill 6 to 83 if the thread index is not opaque to each range)."""
 
 import os
 import re
@@ -15,9 +15,6 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2606_02544_amd", "csrc")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-
-# Rotary stream variants: spills allowed up to this many VGPRs.
-ALLOWED = {"attn_bf16_stream": 40}
 
 
 def spills(source):
@@ -46,12 +43,5 @@ def spills(source):
 def test_no_vgpr_spills(source):
     found = spills(source)
     assert found, "no kernel resource remarks parsed"
-    bad = []
-    for name, n in found.items():
-        if n == 0:
-            continue
-        rotary_stream = "attn_bf16_stream" in name and re.search(r"ELb[01]ELb1EEEv", name)
-        limit = ALLOWED["attn_bf16_stream"] if rotary_stream else 0
-        if n > limit:
-            bad.append((name, n))
+    bad = [(name, n) for name, n in found.items() if n]
     assert not bad, f"VGPR spills: {bad}"
