@@ -838,7 +838,8 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
 //
 // What bounds it: the fp32 products, 256 flop per cycle and CU (a 16-key
 // sub-tile is 2 * RB * D / 4 * 32 MFMA cycles per wave, 1.7 us at RB = 2 and
-// D = 128), while the next sub-tile's K and V load into a second register set.
+// D = 128), while the next sub-tile's K and V load into the registers this one
+// has freed.
 // Both products use v_mfma_f32_16x16x4_f32, whose operands are one float per
 // lane, so a lane's 16-byte loads become operands as they are:
 //   S^T = K Q^T: lane (n = lane % 16, q = lane / 16) holds dims 16 i + 4 q + e
@@ -848,10 +849,10 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
 //     scores is key 4 q + j of row n already, the B operand without a shuffle;
 //     the V^T operand is key 4 q + j, dim 64 u + 4 n + e, register e of the
 //     16-byte load (j, u).
-// Measured, kernel time at batch 1, 32/8 heads, D 128, 16 new slots: prefix 1024
-// 11.8 us (54.9 us with fp32 vector FMAs and per-row state in LDS, the kernel
-// this one replaced); prefix 8192 with 64 new slots 105 us, 83 TFLOP/s of the
-// 153 a large fp32 matrix product reaches.
+// Measured, kernel time at batch 1, 32/8 heads, D 128: 16 new slots, prefix 1024
+// (RB = 1) 11.9 us (54.9 us with fp32 vector FMAs and per-row state in LDS, the
+// kernel this one replaced); 64 new slots, prefix 8192 (RB = 2) 106 us, 82
+// TFLOP/s of the 153 a large fp32 matrix product reaches.
 // ----------------------------------------------------------------------------
 __device__ inline float quad_max(float x) {      // over lanes l, l ^ 16, l ^ 32, l ^ 48
   const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
@@ -1170,17 +1171,14 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
 }
 
 // ----------------------------------------------------------------------------
-// Merge of few split partials.  Grid: (thread blocks over the packed rows of a
-// row block, KV head x row block, sequence); one thread per (row, DPT dims of
-// the output): 16 bytes of each partial, 8 dims of a bf16 partial or 4 of an
-// fp32 one.  Sequences whose prefix fits one chunk were finished by the attention kernel
-// and are skipped.
-// ----------------------------------------------------------------------------
-// Merge of the partials of each pair.  Chunked decomposition: the pair's
-// nsplit chunk partials.  Stream decomposition: the partials of the groups
-// g_first..g_last whose tile ranges meet the pair (slot 1 of g_first when the
-// pair starts inside its range, slot 0 otherwise); a pair inside one group's
-// range was written whole by that group.
+// Merge of a pair's few partials: up to four chunks (more: merge_wide_kernel),
+// or, in the stream decomposition, the groups g_first..g_last whose tile ranges
+// meet the pair (slot 1 of g_first when the pair starts inside its range, slot 0
+// otherwise).  Grid: (thread blocks over the packed rows of a row block, KV head
+// x row block, sequence); one thread per (row, DPT dims of the output): 16 bytes
+// of each partial, 8 dims of a bf16 partial or 4 of an fp32 one.  A pair whose
+// prefix fits one chunk, or that lies inside one group's range, was written
+// whole by the attention kernel and is skipped.
 // SB partials are loaded per round (indices clamped, so a round always loads
 // SB); the launcher takes SB near the split count.
 template <int D, typename OutT, bool STREAM, int SB, typename PartT = OutT>
