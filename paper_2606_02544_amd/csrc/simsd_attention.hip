@@ -1027,6 +1027,12 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
     l_run[r] = 0.f;
   }
   const float sl2 = a.scale_log2;
+  // m_run is the running maximum (log2 units) rounded up to a whole number: the
+  // state is rescaled by exact powers of two, only when the maximum passes one,
+  // and no weight exceeds 1 (values near the largest float do not overflow).
+  // The scale goes into the exponent's FMA, except past 2^24, where the exact
+  // product differs from the rounded maximum by more than 1 and would take all
+  // weights to 0 or infinity: there it rounds first, as the maximum did.
 
   // One item per round: scores of its 16 keys, the rows' running state, the
   // output.  Its K registers are free after the scores and its V registers
@@ -1077,18 +1083,27 @@ __global__ void __launch_bounds__(256, 2) attn_f32_kernel(AttnArgs a) {
 #pragma unroll
     for (int r = 0; r < RB; ++r) {
       const float mx = quad_max(fmaxf(fmaxf(s[r][0], s[r][1]), fmaxf(s[r][2], s[r][3])));
-      const float m_new = fmaxf(m_run[r], mx * sl2);
-      if (m_new > m_run[r] + kLazy) {
-        const float alpha = __builtin_amdgcn_exp2f(m_run[r] - m_new);
+      const float m_new = mx * sl2;
+      if (m_new > m_run[r]) {
+        const float up = ceilf(m_new);
+        const float alpha = __builtin_amdgcn_exp2f(m_run[r] - up);
         l_run[r] *= alpha;
 #pragma unroll
         for (int c = 0; c < D / 16; ++c) o[r][c] *= alpha;
-        m_run[r] = m_new;
+        m_run[r] = up;
       }
       const float moff = m_run[r] == kNegInf ? 0.f : m_run[r];
+      if (__builtin_expect(__any(fabsf(moff) > 0x1p24f), 0)) {
+#pragma clang fp contract(off)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[r][j] = s[r][j] * sl2 - moff;
+      } else {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) s[r][j] = fmaf(s[r][j], sl2, -moff);
+      }
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        s[r][j] = __builtin_amdgcn_exp2f(fmaf(s[r][j], sl2, -moff));
+        s[r][j] = __builtin_amdgcn_exp2f(s[r][j]);
         l_run[r] += s[r][j];
       }
     }

@@ -65,3 +65,40 @@ def test_f32_infinite_last_value(prefix, B, L):
     assert np.all(out[:, -1, :, 7] == np.inf)
     rest = np.delete(np.arange(64), (3, 7, 40))
     np.testing.assert_array_equal(out[..., rest], clean[..., rest])
+
+
+@pytest.mark.parametrize("prefix,scale", [(90, 1e18), (90, 1e4), (700, 3e9), (5, 1e18)])
+def test_f32_huge_scores(prefix, scale):
+    """Scores past 2^24 and up to near the largest float: the largest one takes
+    all the weight, and its row's output is that key's value."""
+    cfg = VerifyConfig(0, "f32", "f32", batch=2, num_q_heads=8, num_kv_heads=2, head_dim=64,
+                       prefix=(prefix, prefix), block_size=8, max_ref=5, vocab=100, qkv_std=1.0)
+    inp = generate(cfg, seed=560 + prefix)
+    for x in (inp.q, inp.k_new, inp.k_cache):
+        x *= np.float32(scale)
+    ref_out, ref_lse = oracle.verify_attention(inp)
+    assert np.abs(ref_lse).max() > 1e7
+    for chunk in (0, 64):
+        out, lse = run_attention(DeviceInputs(inp), chunk)
+        check_attention(out, lse, ref_out, ref_lse, "f32")
+
+
+def test_f32_huge_values():
+    """Values near the largest float, at a key whose score passes those before
+    it: their weighted sum, three times 1e38 at most, does not overflow."""
+    d, prefix = 64, 300
+    cfg = VerifyConfig(0, "f32", "f32", batch=1, num_q_heads=4, num_kv_heads=2, head_dim=d,
+                       prefix=(prefix, prefix), block_size=8, max_ref=8, vocab=100, qkv_std=1.0)
+    inp = generate(cfg, seed=580)
+    u = inp.q[0, 0, 0].copy()
+    inp.q[:] = u
+    for key in (70, 180, 299):                 # second to fifth sub-tiles of their waves
+        inp.k_cache[0, key] = u * (4.5 * np.sqrt(d) / np.dot(u, u))
+        inp.v_cache[0, key, :, 9] = 1e38
+    ref_out, ref_lse = oracle.verify_attention(inp)
+    assert 3e37 < ref_out[..., 9].min()
+    rest = np.delete(np.arange(d), 9)
+    for chunk in (0, 64, 320):
+        out, lse = run_attention(DeviceInputs(inp), chunk)
+        np.testing.assert_allclose(out[..., 9], ref_out[..., 9], rtol=1e-5)
+        check_attention(out[..., rest], lse, ref_out[..., rest], ref_lse, "f32")
