@@ -850,8 +850,8 @@ __global__ void __launch_bounds__(RW * KW * 64, 2) attn_bf16_stream(AttnArgs a) 
 //     the V^T operand is key 4 q + j, dim 64 u + 4 n + e, register e of the
 //     16-byte load (j, u).
 // Measured, kernel time at batch 1, 32/8 heads, D 128: 16 new slots, prefix 1024
-// (RB = 1) 11.9 us (54.9 us with fp32 vector FMAs and per-row state in LDS, the
-// kernel this one replaced); 64 new slots, prefix 8192 (RB = 2) 106 us, 82
+// (RB = 1) 12.3 us (54.9 us with fp32 vector FMAs and per-row state in LDS, the
+// kernel this one replaced); 64 new slots, prefix 8192 (RB = 2) 110 us, 79
 // TFLOP/s of the 153 a large fp32 matrix product reaches.
 // ----------------------------------------------------------------------------
 __device__ inline float quad_max(float x) {      // over lanes l, l ^ 16, l ^ 32, l ^ 48
