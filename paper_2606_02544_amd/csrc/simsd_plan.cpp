@@ -117,7 +117,6 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p, bool
   if (static_cast<int64_t>(d->num_kv_heads) * r.row_blocks > 65535)
     return fail(SIMSD_ERR_BAD_SHAPE, "attention: num_kv_heads * row blocks exceeds 65535");
   r.pairs = static_cast<int64_t>(d->batch) * d->num_kv_heads * r.row_blocks;
-  bool clamped = false;   // automatic chunks at their longest: several rounds of work-groups
   if (d->kv_chunk > 0) {
     r.chunk = d->kv_chunk;
   } else {
@@ -129,8 +128,7 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p, bool
     int64_t c = ceil_div(static_cast<int64_t>(d->max_prefix_len) * r.pairs, target);
     c = ceil_div(c, kTile) * kTile;
     if (c < kMinAutoChunk) c = kMinAutoChunk;
-    clamped = c > kMaxAutoChunk;
-    if (clamped) c = kMaxAutoChunk;
+    if (c > kMaxAutoChunk) c = kMaxAutoChunk;
     r.chunk = static_cast<int>(c);
   }
   r.splits = d->max_prefix_len > 0 ? static_cast<int>(ceil_div(d->max_prefix_len, r.chunk)) : 1;
@@ -148,16 +146,18 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p, bool
   // lengths are on the device.  Workspace: two partial slots per group, then the
   // per-sequence tile offsets.
   //
-  // Row blocks of 256 rows stream only where the chunks would cut the longest
-  // pairs in two, a grid that fills its rounds badly even with equal prefixes:
-  // chunks us / stream us, D 128, 8 KV heads: 17 sequences of 1024 67 / 58, of
-  // 100..1024 50 / 48, of 8192 271 / 206; 24 of 4096 209 / 164, of 100..4096
-  // 166 / 101; 31 of 100..8192 346 / 200.  Pairs of one chunk each are dealt to
-  // free CUs whole and need no merge (64 of 4096 331 / 363; 48 of 1024 94 / 111,
-  // of 100..1024 77 / 84), more than two chunks balance by themselves (11 of
-  // 100..2048 39 / 45), and chunks at their longest make full rounds (31 of 16384
-  // 642 / 711): there the chunks stay, though some uneven batches would be
-  // faster as a stream (48 of 100..4096 205 / 179; 31 of 100..16384 486 / 385).
+  // Row blocks of 256 rows stream where the chunks would cut pairs, a grid of
+  // unlike groups that fills its rounds badly: chunks us / stream us, 8 KV heads,
+  // 256 rows unless said: 17 sequences of 1024 67 / 58, of 8192 271 / 206; 24 of
+  // 100..4096 166 / 101; rotary, 7 of 2352 with 352 rows 92 / 73; 17 of 9984 with
+  // 384 rows, d 64 492 / 271; 37 of 800..15587, 4 KV heads, rotary 365 / 237.
+  // (Slower: equal prefixes of just two longest chunks, 31 of 16384 642 / 711, and
+  // some uneven batches of short ones, 11 of 100..2048 39 / 45; the lengths are on
+  // the device.)  Whole pairs are dealt to free CUs and need no merge, so they
+  // keep the chunks (64 of 4096 331 / 363; 48 of 1024 94 / 111; 31 of 862 with
+  // 352 rows, rotary 92 / 121) but for less than one and a half rounds of long
+  // ones, whose second round is half empty: 17 of 200..5107 with 512 rows, d 64
+  // 226 / 160; 39 of 6068 411 / 369; 20 of 3144 with 352 rows 132 / 122.
   const bool can_stream = d->dtype == SIMSD_BF16 && d->batch <= kMaxStreamBatch;
   if (d->kv_chunk == kStreamChunk && !(can_stream && r.row_waves <= 4))
     return fail(SIMSD_ERR_UNSUPPORTED,
@@ -167,7 +167,8 @@ simsd_status plan_attention(const simsd_attn_desc* d, int cus, AttnPlan* p, bool
     // Stream groups: 8 waves (one per CU) for four or eight row waves, else 4 (two per CU).
     const int64_t groups = r.row_waves >= 4 ? cus : 2 * int64_t{cus};
     const int64_t tiles = r.pairs * (ceil_div(d->max_prefix_len, kTile) + 1);
-    const bool fits = r.row_waves <= 4 || (r.splits == 2 && !clamped && !spare);
+    const bool half_round = r.pairs * 2 < 3 * groups && d->max_prefix_len >= 2048;
+    const bool fits = r.row_waves <= 4 || (!spare && (r.splits >= 2 || half_round));
     if (d->kv_chunk == kStreamChunk || (fits && tiles >= 8 * groups && r.pairs * r.splits > groups)) {
       r.stream = true;
       r.stream_groups = static_cast<int>(groups);

@@ -97,19 +97,21 @@ static AttnPlan auto_plan(int batch, int prefix, int slots) {
 }
 
 static void decomposition_cases() {
-  // 256-row blocks: stream where the chunks would cut the longest pairs in two.
-  for (const auto& c : {std::pair<int, int>{17, 1024}, {17, 8192}, {24, 4096}, {31, 8192}}) {
+  // 256-row blocks: stream where the chunks would cut pairs, and for less than
+  // one and a half rounds of long whole pairs.
+  for (const auto& c : {std::pair<int, int>{17, 1024}, {17, 8192}, {24, 4096}, {31, 8192}, {11, 2048},
+                        {13, 5000}, {31, 16384}, {64, 32768}, {33, 4096}, {33, 2048}, {47, 2048}}) {
     const AttnPlan p = auto_plan(c.first, c.second, 32);
     EXPECT(p.stream && p.row_waves == 8 && p.stream_groups == kCUs && p.seg_tiles == 6);
     EXPECT(p.workspace == size_t{256} * 2 * 256 * 130 * 4 + 257 * 8);
   }
-  // Pairs of one chunk each: no stream and no workspace.
-  for (const auto& c : {std::pair<int, int>{33, 4096}, {64, 4096}, {64, 1024}, {60, 1000}, {48, 2048}}) {
+  // Other whole pairs: no stream and no workspace.
+  for (const auto& c : {std::pair<int, int>{33, 2047}, {48, 4096}, {64, 4096}, {64, 1024}, {60, 1000}, {48, 2048}}) {
     const AttnPlan p = auto_plan(c.first, c.second, 32);
     EXPECT(!p.stream && p.splits == 1 && p.workspace == 0);
   }
-  // Small batches cut into more chunks, and chunks at their longest.
-  for (const auto& c : {std::pair<int, int>{11, 2048}, {13, 5000}, {31, 16384}, {64, 32768}})
+  // One round of chunks, and few tiles.
+  for (const auto& c : {std::pair<int, int>{8, 8192}, {16, 16384}, {4, 2048}})
     EXPECT(!auto_plan(c.first, c.second, 32).stream);
   // Smaller row blocks stream past one round of groups.
   AttnPlan p = auto_plan(64, 4096, 16);

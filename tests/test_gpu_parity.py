@@ -227,8 +227,8 @@ def takes_stream(d, hq, hkv, B, L, batch, max_prefix):
          "212rows-paged-rope-stream", "496rows-paged-stream"])
 def test_stream_whole_row_blocks(d, hq, B, L, batch, page, theta, longest):
     """Row blocks of more than 128 rows take the stream decomposition by
-    themselves where the chunks would cut the longest pairs in two; pairs of one
-    chunk each stay whole, in several rounds of groups."""
+    themselves where the chunks would cut pairs; short pairs of one chunk each stay
+    whole, in several rounds of groups."""
     assert takes_stream(d, hq, 8, B, L, batch, longest) == (longest == 1100)
     cfg = VerifyConfig(0, "blocks", "bf16", batch=batch, num_q_heads=hq, num_kv_heads=8, head_dim=d,
                        prefix=(0, longest), block_size=B, max_ref=L, vocab=100, page_size=page,
